@@ -76,7 +76,9 @@ def traffic_entry(kernel_key: str):
 
 
 def step_kernel_name(storage: str, wl) -> str:
-    """The step kernel the library launches for this storage and grid size."""
+    """The step kernel of a workload here: what AUTO launches on grids of at least 3 * 2^18 cells;
+    below that the storage's one-thread-per-cell kernel (``kernel="tile"`` or ``"cell"``), where
+    AUTO takes the plane-group kernel instead."""
     big = wl.nx * wl.ny >= 3 << 18
     if storage == "f64":
         return "k_collide_advect_sweep" if big else "k_collide_advect_lds"

@@ -76,15 +76,16 @@ enum dvbm_storage { DVBM_F64 = 0, DVBM_F32 = 1, DVBM_BF16_DEV = 2, DVBM_FP16_DEV
  * (thermal Couette flow, Sec. IV).  The wall's two ghost rows take the fields
  * of the first two interior rows reflected through the wall values,
  * rho_G = rho_B, u_G = 2 u_W - u_B, T_G = 2 T_W - T_B, and the populations
- * X^eq(G) + (X_B - X^eq(B)).  Walls run on the per-cell kernel, need the
- * larger workspace dvbm_workspace_bytes() reports for them, and have no
+ * X^eq(G) + (X_B - X^eq(B)).  Walls run on the plane-group kernel (AUTO) or
+ * the per-cell kernel (CELL), need the larger workspace dvbm_workspace_bytes() reports for them, and have no
  * adjoint (EINVAL). */
 enum dvbm_bc { DVBM_PERIODIC = 0, DVBM_ZERO_GRADIENT = 1, DVBM_WALL = 2 };
 enum dvbm_visc { DVBM_CONST_MU = 0, DVBM_CONST_TAU = 1 };
 /* Step kernel (all compute the same update; the choice only affects speed):
- * AUTO picks the column sweep on grids of at least 3 * 2^18 cells (for
- * 32/16-bit storage only when one distribution fits 2 GiB), else the LDS
- * tile kernel for DVBM_F64 and the per-cell kernel for the other storages.
+ * AUTO picks the column sweep on grids of at least 3 * 2^18 cells without
+ * walls (for 32/16-bit storage only when one distribution fits 2 GiB, else the
+ * per-cell kernel), and the plane-group kernel, which has no value of its own
+ * here, on smaller grids and with walls.
  * SWEEP with 32/16-bit storage requires a distribution of at most 2 GiB. */
 enum dvbm_kernel { DVBM_KERNEL_AUTO = 0, DVBM_KERNEL_CELL = 1, DVBM_KERNEL_SWEEP = 2, DVBM_KERNEL_TILE = 3 };
 

@@ -1,11 +1,12 @@
 // MI355X (gfx950) implementation of the DDF-QE DVBM hot path and its C ABI.
 //
 // Kernels:
-//   k_collide_advect  one full time step of Eq. (finalDiscretePDE): moments,
+//   k_collide_advect*  one full time step of Eq. (finalDiscretePDE): moments,
 //                     (quasi-)equilibria, two-time relaxation and NND flux
-//                     divergence of every population, fused; one thread per
-//                     cell, populations read once from HBM as coalesced
-//                     structure-of-arrays rows, flux stencils from LDS tiles.
+//                     divergence of every population, fused: the column sweep
+//                     (_sweep) on large grids, plane groups (_planes) on
+//                     smaller ones and with walls, one thread per cell with
+//                     the stencils through the caches or, in _lds, LDS tiles.
 //   k_init            equilibrium populations of macroscopic fields (Sec. III A 3).
 //   k_moments         rho, u, T fields and per-block float64 conservation sums.
 //   k_speed           per-block extrema of the initial fields (time step, checks).
@@ -23,18 +24,12 @@
 #include "lattice.h"
 #include "node.h"
 #include "step.h"
+#include "planes.h"
 #include "sweep.h"
 #include "adjoint.h"
 
 namespace dvbm {
 
-// Two step kernels, chosen per storage format by measurement on MI355X:
-//  - per-cell (register) kernel: a cell's 2Q populations live in registers,
-//    flux stencils come through the vector L1/L2 (float32 and 16-bit
-//    storage);
-//  - LDS-tiled kernel: groups of N1 population planes are staged with their
-//    ghost layers in LDS (float64 storage, whose larger rows make the cache
-//    path the bottleneck).
 constexpr int RED_BLOCKS = 1024;
 constexpr int RED_THREADS = 256;
 // blocks of the adjoint relaxation kernel (their partials fit the
@@ -82,9 +77,6 @@ __device__ inline void tile_of_block(int w, int nbx, int nby, int& bx, int& by) 
   by = t % nby;
 }
 
-#ifndef DVBM_SWEEP
-#define DVBM_SWEEP 1
-#endif
 // ------------------------------------------------------------ fused step
 // At most two waves per SIMD: the cell's stencil loads (about 290) are then
 // all issued ahead of their uses.  Left to aim at a higher occupancy, the
@@ -111,6 +103,51 @@ __global__ __launch_bounds__(TILE_TX* TILE_TY) void k_collide_advect_lds(const t
   int bx, by;
   tile_of_block(blockIdx.x, (kp.nx + TILE_TX - 1) / TILE_TX, (kp.ny + TILE_TY - 1) / TILE_TY, bx, by);
   tile_update<SPLIT, S, BCX, BCY, PRM, TILE_TX, TILE_TY>(src, dst, kp, bx, by, lds);
+}
+
+// Plane-group kernel: workgroup b is logical (strip, row range) L, strips
+// fastest, dealt so that every XCD gets one contiguous range of L (neighbouring
+// ranges read each other's edge rows from the XCD's L2).  Two workgroups fit a
+// CU in 32/16-bit storage: the register cap costs a few spilled registers
+// (f32_dev 256^2: 11.3 us uncapped at 86 registers and one workgroup, 9.6 us
+// capped at 80); float64 needs 153 registers and runs one.
+template <class S>
+constexpr int planes_wpe() {
+  return sizeof(typename S::T) == 8 ? 3 : 6;
+}
+template <int SPLIT>
+constexpr int planes_threads() {
+  return 128 * (Set<SPLIT>::N1 + 1);
+}
+template <int SPLIT, class S, int BCX, int BCY, int PRM>
+__global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(planes_wpe<S>()))) void
+k_collide_advect_planes(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst, KParams kp,
+                        const typename S::T* __restrict__ ghost, int nstrips, int nranges) {
+  constexpr int N1 = Set<SPLIT>::N1;
+  __shared__ PlanesShared<SPLIT, typename S::C> sh;
+  const int nb = int(gridDim.x), blk = int(blockIdx.x);
+  const int xcd = blk % 8, k = blk / 8, base = nb / 8, rem = nb % 8;
+  const int L = xcd < rem ? xcd * (base + 1) + k : rem * (base + 1) + (xcd - rem) * base + k;
+  const int j = int(unsigned(L) / unsigned(nstrips)), strip = L - j * nstrips;
+  // nranges ranges of ny / nranges rows, the first ny % nranges of them one longer
+  const int rows = int(unsigned(kp.ny) / unsigned(nranges)), longer = kp.ny - rows * nranges;
+  const int ya = j * rows + (j < longer ? j : longer), yb = ya + rows + (j < longer ? 1 : 0);
+  const int x0 = strip * SWEEP_OWN;
+  // Role of the wave: plane waves of f (a), of g (N1 + a), coefficients of f
+  // and g.  With N1 = 5 the waves of one SIMD (every fourth) get f 0, g 0, f 2;
+  // f 1, g 1, g 2; f 3, g 3 and g's coefficients; f 4, g 4 and f's: with the
+  // planes of xi = 0 (no x flux) and the coefficients spread, the four carry
+  // within 6 % of the mean; in plain order one carries 20 % more.
+  int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
+  if (N1 == 5) w = int(0xAB7298654310ull >> (4 * w)) & 15;
+  if (w < N1)
+    planes_walk<SPLIT, S, BCX, BCY, 0>(src, dst, kp, w, x0, ya, yb, ghost, sh);
+  else if (w < 2 * N1)
+    planes_walk<SPLIT, S, BCX, BCY, 1>(src, dst, kp, w - N1, x0, ya, yb, ghost, sh);
+  else if (w == 2 * N1)
+    planes_coeffs<SPLIT, S, PRM, 0>(kp, yb - ya, sh);
+  else
+    planes_coeffs<SPLIT, S, PRM, 1>(kp, yb - ya, sh);
 }
 
 // Row range j of kseg in a column of ny rows for the column sweep: ranges of
@@ -141,8 +178,10 @@ __device__ inline void sweep_range(int ny, int kseg, int j, int u, int& ya, int&
 #define DVBM_SWEEP_WPE 2
 #endif
 // Below this many cells a grid has too few strip groups x row ranges to
-// occupy the device, and the per-cell kernel is faster (measured: 256^2 and
-// 512^2 favour it, 1024^2 and larger the sweep).
+// occupy the device, and the plane-group kernel is faster: us per step,
+// planes / sweep, float64 512^2 39 / 60, 800^2 124 / 125; float32 deviations
+// 512^2 21.8 / 44, 800^2 54.9 / 54.0; and above it float64 1024^2 192 / 196,
+// float32 1024^2 113 / 105, 4096^2 1590 / 1446.
 constexpr int64_t SWEEP_MIN_CELLS = 3 << 18;
 #ifndef DVBM_SWEEP_K64
 #define DVBM_SWEEP_K64 2  // strips per workgroup, float64 storage
@@ -701,6 +740,7 @@ struct dvbm_handle {
   hipStream_t stream;
   double dt;
   mutable int sweep_kseg;  // row ranges per strip of the column-sweep kernel (0: not chosen yet)
+  mutable int planes_ranges;  // the same of the plane-group kernel
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -748,6 +788,39 @@ KParams make_kparams(const dvbm_params& p, double dt) {
 #ifndef DVBM_SWEEP_ROUNDS16
 #define DVBM_SWEEP_ROUNDS16 1
 #endif
+// Compute units of the current device and workgroups of `kern` each of them
+// holds at a time (256 and 1 where the runtime does not say).
+void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
+  int dev = 0;
+  ncu = per_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0) != hipSuccess || ncu <= 0 || per_cu <= 0) {
+    (void)hipGetLastError();
+    ncu = 256;
+    per_cu = 1;
+  }
+}
+
+// Row ranges per strip of the plane-group kernel.  A range costs about three
+// row steps before its first row is stored, and a second round of workgroups
+// costs them again, so all workgroups run at once: one per CU, or two where
+// they fit and leave ranges of at least 4 rows (f32_dev, 256^2: 8.95 us with
+// 255 ranges of 5 rows, 9.55 us with 510 of 2.5; 512^2: 22.8 us with 252,
+// 21.8 us with 504; three per CU, split I: 14.3 us against 12.7 us at 509 x 383).
+// Ranges that would be longer than 32 rows are cut to 16, in more rounds:
+// neighbouring workgroups then stay close in memory (float64 1024^2: 206 us in
+// one round of 68 rows, 192 us at 9 rows; f32 4096^2: 1590 us at 8 to 16 rows,
+// 1790 us at 32).
+int planes_ranges(const void* kern, int block, int nstrips, int ny) {
+  int ncu, per_cu;
+  device_slots(kern, block, ncu, per_cu);
+  int n = per_cu >= 2 ? 2 * ncu / nstrips : 0;
+  if (n < 1 || ny / n < 4) n = ncu / nstrips;
+  if (n < 1 || ny / n > 32) n = ny / 16;
+  return n < 1 ? 1 : (n > ny ? ny : n);
+}
+
 // Row ranges per strip group for the column sweep.  One workgroup fits a
 // CU at a time, so one round of ranges (as many workgroups as the device
 // holds) ends with its slowest CU; `rounds` rounds of shorter ranges let the
@@ -757,14 +830,8 @@ KParams make_kparams(const dvbm_params& p, double dt) {
 // wave: float64 storage gains 15 % at 6 rounds, float32 4.5 % at 4 rounds,
 // the 16-bit formats nothing.
 int sweep_ranges(const void* kern, int block, int ngroups, int ny, int rounds, int unit) {
-  int dev = 0, ncu = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0) != hipSuccess || ncu <= 0 || per_cu <= 0) {
-    (void)hipGetLastError();
-    ncu = 256;
-    per_cu = 1;
-  }
+  int ncu, per_cu;
+  device_slots(kern, block, ncu, per_cu);
   const int one = ncu * per_cu / ngroups;  // ranges per strip group in one round
   int want = rounds * one < ny / 48 ? rounds * one : ny / 48;
   if (want < one) want = one;
@@ -783,15 +850,14 @@ int sweep_ranges(const void* kern, int block, int ngroups, int ny, int rounds, i
 namespace dvbm_launch {
 
 // The kernel a handle's steps use (the AUTO rule of dvbm_kernel).
+constexpr int KERNEL_PLANES = -1;  // the plane-group kernel: chosen by AUTO only
 inline int step_kernel(const dvbm_handle* h) {
-  if (h->p.bc_y == DVBM_WALL) return DVBM_KERNEL_CELL;
   if (h->p.kernel != DVBM_KERNEL_AUTO) return h->p.kernel;
   const bool big = int64_t(h->p.nx) * h->p.ny >= SWEEP_MIN_CELLS;
-  if (h->p.storage == DVBM_F64) return DVBM_SWEEP && big ? DVBM_KERNEL_SWEEP : DVBM_KERNEL_TILE;
+  if (h->p.bc_y == DVBM_WALL || !big) return KERNEL_PLANES;
+  if (h->p.storage == DVBM_F64) return DVBM_KERNEL_SWEEP;
   const uint64_t dist = uint64_t(h->kp.sdist) * uint64_t(storage_bytes(h->p.storage));
-  if (DVBM_SWEEP && big && dist <= (uint64_t(1) << 31))
-    return DVBM_KERNEL_SWEEP;
-  return DVBM_KERNEL_CELL;
+  return dist <= (uint64_t(1) << 31) ? DVBM_KERNEL_SWEEP : DVBM_KERNEL_CELL;
 }
 
 template <int SPLIT, class S, int BCX, int BCY, int PRM>
@@ -799,16 +865,28 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
   using T = typename S::T;
   const T* s = static_cast<const T*>(src);
   T* d = static_cast<T*>(dst);
+  const int kern_id = step_kernel(h);
+  T* gh = nullptr;
   if constexpr (BCY == BC_WALL) {
-    T* gh = reinterpret_cast<T*>(h->ws + WS_GHOST);
+    gh = reinterpret_cast<T*>(h->ws + WS_GHOST);
     hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream, s, gh,
                        h->kp);
+  }
+  if (kern_id == KERNEL_PLANES) {
+    const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY, PRM>;
+    const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
+    if (h->planes_ranges == 0)
+      h->planes_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
+    hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->planes_ranges)), dim3(planes_threads<SPLIT>()), 0,
+                       h->stream, s, d, h->kp, static_cast<const T*>(gh), nstrips, h->planes_ranges);
+    return;
+  }
+  if constexpr (BCY == BC_WALL) {
     const dim3 grid(((h->p.nx + CELL_TX - 1) / CELL_TX) * ((h->p.ny + CELL_TY - 1) / CELL_TY));
     hipLaunchKernelGGL((k_collide_advect<SPLIT, S, BCX, BCY, PRM>), grid, dim3(CELL_TX, CELL_TY), 0, h->stream, s, d,
                        h->kp, static_cast<const T*>(gh));
     return;
   } else {
-  const int kern_id = step_kernel(h);
   if (kern_id == DVBM_KERNEL_TILE) {
     const dim3 grid(((h->p.nx + TILE_TX - 1) / TILE_TX) * ((h->p.ny + TILE_TY - 1) / TILE_TY));
     hipLaunchKernelGGL((k_collide_advect_lds<SPLIT, S, BCX, BCY, PRM>), grid, dim3(TILE_TX, TILE_TY), 0, h->stream,
@@ -1214,6 +1292,7 @@ int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const d
   h->ws = ws;
   h->stream = s;
   h->sweep_kseg = 0;
+  h->planes_ranges = 0;
   // the fixed scratch of dvbm_adjoint_step_noalloc on this device (set-up only:
   // that entry point then makes no runtime call besides its launches)
   h->scratch = nullptr;

@@ -122,6 +122,16 @@ __device__ inline R lim4(R a, R b, R beta2) {
   return med3(med3(beta2 * a, beta2 * b, R(0)), a + b, R(0));
 }
 
+// The same in float64, where the hardware has no three-way median: with equal
+// signs min(2 beta |a|, 2 beta |b|, |a + b|) = min(2 beta min(|a|, |b|), |a + b|)
+// carries the common sign, else 0 (9 vector instructions; two medians
+// written out take 11).
+__device__ inline double lim4(double a, double b, double beta2) {
+  const double s = a + b, m = fmin(beta2 * fmin(fabs(a), fabs(b)), fabs(s));
+  const int sa = int(__builtin_bit_cast(uint64_t, a) >> 32), sb = int(__builtin_bit_cast(uint64_t, b) >> 32);
+  return (sa ^ sb) < 0 ? 0.0 : copysign(m, s);
+}
+
 // X_{c+1/2} - X_{c-1/2} of the NND reconstruction for a positive velocity
 // component; m2, m1, c0, p1 are the values at c-2 .. c+1:
 //   (c0 + L(d1, d2)) - (m1 + L(d0, d1)) = d1 + (L(d1, d2) - L(d0, d1)).
@@ -188,106 +198,58 @@ __device__ inline NodeMoments node_moments(const R* f, const R* g) {
   return m;
 }
 
-// Float64 moments (Eqs. eq_quadratur1-3, Table I notation) of one
-// distribution, accumulated one pair of +-xi_a columns at a time: the ten
-// moments of orders 0-3 of f (D = 0) or the three of orders 0-1 of g (D = 1).
-template <int D, int N1, class R>
-__device__ inline void half_moments(const R* v, double* out) {
+// The same sums of w_b v_b, for values v in units of the weight (the
+// deviations the deviation formats store): the weights enter the float64
+// coefficients of the sums, so no value is scaled first.
+template <int N1, class V>
+__device__ inline void weighted_pair_sums(const V* v, double& s0, double& s1, double& s2, double& s3) {
   using L = GH<N1>;
-  constexpr int NM = D == 0 ? 10 : 3;
-  double acc[NM];
-  double u1, u2, u3;
-  if (L::has_zero) {
-    constexpr int a = N1 / 2;
-    double s0, s1, s2, s3;
-    pair_sums<N1>(v + a * N1, s0, s1, s2, s3);
-    if (D == 0) {
-      // rho, jx, jy, pxx, pxy, pyy, qxxx, qxxy, qxyy, qyyy
-      acc[0] = s0; acc[1] = 0.0; acc[2] = s1; acc[3] = 0.0; acc[4] = 0.0;
-      acc[5] = s2; acc[6] = 0.0; acc[7] = 0.0; acc[8] = 0.0; acc[9] = s3;
-    } else {
-      // g0, qgx, qgy
-      acc[0] = s0; acc[1] = 0.0; acc[2] = s1;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < NM; ++k) acc[k] = 0.0;
-  }
-  (void)u1; (void)u2; (void)u3;
+  s0 = L::has_zero ? L::w(N1 / 2) * double(v[N1 / 2]) : 0.0;
+  s1 = s2 = s3 = 0.0;
 #pragma unroll
   for (int k = 0; k < N1 / 2; ++k) {
-    const int pa = N1 - 1 - k;
-    const double x = L::xi(pa);
-    double a0, a1, a2, a3, b0, b1, b2, b3;
-    pair_sums<N1>(v + pa * N1, a0, a1, a2, a3);
-    pair_sums<N1>(v + k * N1, b0, b1, b2, b3);
-    const double e0 = a0 + b0, o0 = a0 - b0, e1 = a1 + b1;
-    if (D == 0) {
-      const double o1 = a1 - b1, e2 = a2 + b2, o2 = a2 - b2;
-      acc[0] += e0;
-      acc[1] += x * o0;
-      acc[2] += e1;
-      acc[3] += (x * x) * e0;
-      acc[4] += x * o1;
-      acc[5] += e2;
-      acc[6] += (x * x * x) * o0;
-      acc[7] += (x * x) * e1;
-      acc[8] += x * o2;
-      acc[9] += a3 + b3;
-    } else {
-      acc[0] += e0;
-      acc[1] += x * o0;
-      acc[2] += e1;
-    }
+    const int pk = N1 - 1 - k;
+    const double x = L::xi(pk), w = L::w(pk);
+    const double e = double(v[pk]) + double(v[k]), o = double(v[pk]) - double(v[k]);
+    s0 += w * e;
+    s1 += (w * x) * o;
+    s2 += (w * x * x) * e;
+    s3 += (w * x * x * x) * o;
   }
-#pragma unroll
-  for (int k = 0; k < NM; ++k) out[k] = acc[k];
 }
 
-// The same moments of w_i v_i, for values v in units of the weight (the
-// deviations the 16-bit formats store): the weights enter the float64
-// coefficients of the sums, so no value is scaled first.
-template <int D, int N1, class R>
-__device__ inline void half_moments_w(const R* v, double* out) {
+// Float64 moments (Eqs. eq_quadratur1-3, Table I notation) of one
+// distribution from the sums over b of its columns a, accumulated one pair of
+// +-xi_a columns at a time: rho, jx, jy, pxx, pxy, pyy, qxxx, qxxy, qxyy, qyyy
+// of f (D = 0) or g0, qgx, qgy of g (D = 1).  col(a, s0, s1, s2, s3) gives
+// column a's sums of xi_b^k v, k = 0..3 (for g k = 0, 1); W: the sums
+// carry the weights w_b and the columns' own weights w_a are applied here.
+template <int D, int N1, bool W, class F>
+__device__ inline void fold_columns(F&& col, double* out) {
   using L = GH<N1>;
   constexpr int NM = D == 0 ? 10 : 3;
   double acc[NM];
 #pragma unroll
   for (int k = 0; k < NM; ++k) acc[k] = 0.0;
-  // sums over b of w_b v_(a, b) xi_b^k, k = 0..3, folding +-xi_b pairs
-  auto psum = [&](int a, double& s0, double& s1, double& s2, double& s3) {
-    const R* r = v + a * N1;
-    s0 = L::has_zero ? L::w(N1 / 2) * double(r[N1 / 2]) : 0.0;
-    s1 = s2 = s3 = 0.0;
-#pragma unroll
-    for (int k = 0; k < N1 / 2; ++k) {
-      const int pk = N1 - 1 - k;
-      const double x = L::xi(pk), w = L::w(pk);
-      const double e = double(r[pk]) + double(r[k]), o = double(r[pk]) - double(r[k]);
-      s0 += w * e;
-      s1 += (w * x) * o;
-      s2 += (w * x * x) * e;
-      s3 += (w * x * x * x) * o;
-    }
-  };
   if (L::has_zero) {
-    const double wz = L::w(N1 / 2);
+    constexpr int a = N1 / 2;
+    const double w = W ? L::w(a) : 1.0;
     double s0, s1, s2, s3;
-    psum(N1 / 2, s0, s1, s2, s3);
-    acc[0] += wz * s0;
-    acc[2] += wz * s1;
+    col(a, s0, s1, s2, s3);
+    acc[0] = w * s0;
+    acc[2] = w * s1;
     if (D == 0) {
-      acc[5] += wz * s2;
-      acc[9] += wz * s3;
+      acc[5] = w * s2;
+      acc[9] = w * s3;
     }
   }
 #pragma unroll
   for (int k = 0; k < N1 / 2; ++k) {
     const int pa = N1 - 1 - k;
-    const double x = L::xi(pa), w = L::w(pa);
+    const double x = L::xi(pa), w = W ? L::w(pa) : 1.0;
     double a0, a1, a2, a3, b0, b1, b2, b3;
-    psum(pa, a0, a1, a2, a3);
-    psum(k, b0, b1, b2, b3);
+    col(pa, a0, a1, a2, a3);
+    col(k, b0, b1, b2, b3);
     const double e0 = a0 + b0, o0 = a0 - b0, e1 = a1 + b1;
     acc[0] += w * e0;
     acc[1] += (w * x) * o0;
@@ -305,6 +267,22 @@ __device__ inline void half_moments_w(const R* v, double* out) {
   }
 #pragma unroll
   for (int k = 0; k < NM; ++k) out[k] = acc[k];
+}
+
+// The moments of one distribution's populations v (value formats), and of
+// w_i v_i for deviations v in units of the weight.
+template <int D, int N1, class R>
+__device__ inline void half_moments(const R* v, double* out) {
+  fold_columns<D, N1, false>(
+      [&](int a, double& s0, double& s1, double& s2, double& s3) { pair_sums<N1>(v + a * N1, s0, s1, s2, s3); }, out);
+}
+template <int D, int N1, class R>
+__device__ inline void half_moments_w(const R* v, double* out) {
+  fold_columns<D, N1, true>(
+      [&](int a, double& s0, double& s1, double& s2, double& s3) {
+        weighted_pair_sums<N1>(v + a * N1, s0, s1, s2, s3);
+      },
+      out);
 }
 
 // Hermite moments mu_k(u) = sum_j C(k,2j) (2j-1)!! t^j u^(k-2j) of a Gaussian

@@ -34,18 +34,29 @@ __device__ inline double weight(int i) {
 // low-order moments: rho = 1 and P = delta for f (r = 1); for g, g0 = gr0 in
 // both splits (in split I the |xi|^2 - 2 part of r has weighted mean 0) and a
 // zero first moment.
+__device__ inline NodeMoments as_moments(const double* a, const double* b) {
+  NodeMoments m;
+  m.rho = a[0]; m.jx = a[1]; m.jy = a[2];
+  m.pxx = a[3]; m.pxy = a[4]; m.pyy = a[5];
+  m.qxxx = a[6]; m.qxxy = a[7]; m.qxyy = a[8]; m.qyyy = a[9];
+  m.g0 = b[0]; m.qgx = b[1]; m.qgy = b[2];
+  return m;
+}
+__device__ inline NodeMoments add_rest_moments(const double* a, const double* b, const KParams& kp) {
+  NodeMoments m = as_moments(a, b);
+  m.rho += 1.0;
+  m.pxx += 1.0;
+  m.pyy += 1.0;
+  m.g0 += kp.gr0;
+  return m;
+}
 template <int SPLIT, class R>
 __device__ inline NodeMoments dev_moments(const R* df, const R* dg, const KParams& kp) {
   constexpr int N1 = Set<SPLIT>::N1;
   double a[10], b[3];
   half_moments_w<0, N1>(df, a);
   half_moments_w<1, N1>(dg, b);
-  NodeMoments m;
-  m.rho = a[0] + 1.0; m.jx = a[1]; m.jy = a[2];
-  m.pxx = a[3] + 1.0; m.pxy = a[4]; m.pyy = a[5] + 1.0;
-  m.qxxx = a[6]; m.qxxy = a[7]; m.qxyy = a[8]; m.qyyy = a[9];
-  m.g0 = b[0] + kp.gr0; m.qgx = b[1]; m.qgy = b[2];
-  return m;
+  return add_rest_moments(a, b, kp);
 }
 
 template <int BC>

@@ -285,6 +285,36 @@ def test_sweep_strips_and_row_ranges(nx, ny, bc, storage):
     assert rel(f - f0, fo - f0) < tol_inc and rel(g - g0, go - g0) < tol_inc
 
 
+# ---------------------------------------------------------------- plane-group geometry
+@pytest.mark.parametrize("nx,ny", ((4, 4), (59, 5), (60, 7), (63, 6), (64, 9), (61, 40), (121, 13), (130, 2051), (20, 9000)))
+@pytest.mark.parametrize("bc", ("periodic", "zero_gradient", "wall"))
+@pytest.mark.parametrize("storage,split", (("f64", 1), ("f64", 2), ("f32", 2), ("f32_dev", 1), ("bf16_dev", 2),
+                                           ("fp16_dev", 1)))
+def test_plane_group_strips_and_row_ranges(nx, ny, bc, storage, split):
+    """AUTO on grids below the column sweep's: strips of 60 columns (one wrap of the columns suffices from 64 on),
+    one range per row, ranges of unequal length in one round of workgroups, ranges of 16 rows in several; walls read
+    their ghost rows.  Float formats over 4 steps; the 16-bit ones over one, within 1.5 roundings of the deviation."""
+    wl = smooth_random(nx, ny, seed=33, amp_T=0.05)
+    kw = dict(bc_x="periodic", bc_y="wall", wall_T=(0.95, 1.1), wall_ux=(0.0, 0.3)) if bc == "wall" else dict(
+        bc_x=bc, bc_y=bc)
+    s, p = solver(wl, split=split, storage=storage, Pr=0.6, tau_ref=0.02, cfl=0.1, **kw)
+    cfg = oracle_cfg(p)
+    f0, g0 = oracle_state(s)
+    n = 1 if storage in ("bf16_dev", "fp16_dev") else 4
+    s.step(n)
+    f, g = oracle_state(s)
+    fo, go = O.run(f0, g0, cfg, s.dt, n)
+    if n == 1:
+        u = 2.0 ** -8 if storage == "bf16_dev" else 2.0 ** -11
+        dev = fo - O.velocity_set(cfg)[1].reshape(-1, 1, 1)
+        bound = 1.5 * u * float(torch.linalg.vector_norm(dev)) + 1e-6 * float(torch.linalg.vector_norm(fo))
+        assert float(torch.linalg.vector_norm(f - fo)) <= bound
+        return
+    tol, tol_inc = (1e-12, 1e-9) if storage == "f64" else (1e-5, 1e-3)
+    assert rel(f, fo) < tol and rel(g, go) < tol
+    assert rel(f - f0, fo - f0) < tol_inc and rel(g - g0, go - g0) < tol_inc
+
+
 # ---------------------------------------------------------------- 16-bit deviation storage
 @pytest.mark.parametrize("kernel", ("cell", "sweep", "tile"))
 @pytest.mark.parametrize("split", (1, 2))
