@@ -299,7 +299,7 @@ def write_profiles(run_dir: str, workload: str, out_dir: str = os.path.join(ROOT
             sf, _ = _copy_scale(fr, "FETCH_SIZE")
             sw, _ = _copy_scale(wr, "WRITE_SIZE")
             fd, wd = _counter_by_dispatch(fr, "FETCH_SIZE"), _counter_by_dispatch(wr, "WRITE_SIZE")
-            keys = sorted(k for k in at if k[0].startswith(("k_adjoint_relax", "k_adjoint_flux", "k_collide_advect")))
+            keys = sorted(k for k in at if k[0].startswith(("k_adjoint<", "k_adjoint_relax", "k_adjoint_flux", "k_collide_advect")))
             cells = n * n
             fh.write(f"\n## {n} x {n} (calibration x{sf:.3f} fetch, x{sw:.3f} write)\n\n"
                      "| kernel | grid (threads) | calls | average us | read B/cell | written B/cell | GB/s |\n"

@@ -208,8 +208,8 @@ int dvbm_set_state_index(dvbm_handle* h, int index);
 size_t dvbm_adjoint_bytes(const dvbm_params* p);
 
 /* Bytes of the device work array of dvbm_adjoint_step (14 float64 values per
- * cell: the cotangents of the 13 node moments and 1 - dt/tau_1); 0 if the
- * parameters are invalid. */
+ * cell); 0 if the parameters are invalid.  F64 and F32 storage keep these
+ * values on the chip and leave the array as it is; F32_DEV storage writes it. */
 size_t dvbm_adjoint_work_bytes(const dvbm_params* p);
 
 /* lam_n = (dX_{n+1}/dX_n)^T lam_np1 for the step that maps state_n (a device
@@ -218,7 +218,7 @@ size_t dvbm_adjoint_work_bytes(const dvbm_params* p);
  * (dX_{n+1}/dtau_ref)^T lam_np1 and (dX_{n+1}/dPr)^T lam_np1 (at Pr == 1,
  * where Table I has no quasi-equilibrium, the Pr entry is 0), summed in a
  * fixed order through the handle's workspace.  work is a caller-owned device
- * array of dvbm_adjoint_work_bytes() bytes (contents overwritten).  Calls on
+ * array of dvbm_adjoint_work_bytes() bytes (its contents may be overwritten).  Calls on
  * one handle, or sharing one work array, must not overlap; lam_np1 and lam_n
  * must not overlap.  Asynchronous. */
 int dvbm_adjoint_step(dvbm_handle* h, const void* state_n, const double* lam_np1, double* lam_n,

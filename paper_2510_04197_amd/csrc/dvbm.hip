@@ -27,15 +27,16 @@
 #include "planes.h"
 #include "sweep.h"
 #include "adjoint.h"
+#include "adjoint_planes.h"
 
 namespace dvbm {
 
 constexpr int RED_BLOCKS = 1024;
 constexpr int RED_THREADS = 256;
-// blocks of the adjoint relaxation kernel (their partials fit the
-// RED_BLOCKS slots of the workspace)
-constexpr int ADJ_RELAX_BLOCKS = 1024;
-static_assert(ADJ_RELAX_BLOCKS <= RED_BLOCKS, "adjoint partials exceed the workspace");
+// blocks of the adjoint relaxation kernel and most blocks of a launch of the
+// one-sweep adjoint (their partials fit the RED_BLOCKS slots of the workspace)
+constexpr int ADJ_RELAX_BLOCKS = 1024, ADJ_BLOCKS = 1024;
+static_assert(ADJ_RELAX_BLOCKS <= RED_BLOCKS && ADJ_BLOCKS <= RED_BLOCKS, "adjoint partials exceed the workspace");
 // workspace layout (doubles): [0, 4 RED_BLOCKS) block partials, then the
 // final reductions, then (at WS_TICKET) the adjoint's block counter
 constexpr int WS_TICKET = 4 * RED_BLOCKS + 32;
@@ -119,35 +120,53 @@ template <int SPLIT>
 constexpr int planes_threads() {
   return 128 * (Set<SPLIT>::N1 + 1);
 }
-template <int SPLIT, class S, int BCX, int BCY, int PRM>
-__global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(planes_wpe<S>()))) void
-k_collide_advect_planes(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst, KParams kp,
-                        const typename S::T* __restrict__ ghost, int nstrips, int nranges) {
-  constexpr int N1 = Set<SPLIT>::N1;
-  __shared__ PlanesShared<SPLIT, typename S::C> sh;
-  const int nb = int(gridDim.x), blk = int(blockIdx.x);
+__device__ inline void strip_range(int ny, int nstrips, int nranges, int blk, int& strip, int& ya, int& yb) {
+  const int nb = nstrips * nranges;
   const int xcd = blk % 8, k = blk / 8, base = nb / 8, rem = nb % 8;
   const int L = xcd < rem ? xcd * (base + 1) + k : rem * (base + 1) + (xcd - rem) * base + k;
-  const int j = int(unsigned(L) / unsigned(nstrips)), strip = L - j * nstrips;
+  const int j = int(unsigned(L) / unsigned(nstrips));
+  strip = L - j * nstrips;
   // nranges ranges of ny / nranges rows, the first ny % nranges of them one longer
-  const int rows = int(unsigned(kp.ny) / unsigned(nranges)), longer = kp.ny - rows * nranges;
-  const int ya = j * rows + (j < longer ? j : longer), yb = ya + rows + (j < longer ? 1 : 0);
+  const int rows = int(unsigned(ny) / unsigned(nranges)), longer = ny - rows * nranges;
+  ya = j * rows + (j < longer ? j : longer);
+  yb = ya + rows + (j < longer ? 1 : 0);
+}
+// Role of a wave: plane waves of f (a), of g (N1 + a), then the two coefficient
+// waves.  With N1 = 5 the waves of one SIMD (every fourth) get f 0, g 0, f 2;
+// f 1, g 1, g 2; f 3, g 3 and the second coefficient wave; f 4, g 4 and the
+// first: with the planes of xi = 0 (no x flux) and the coefficients spread, the four
+// carry within 6 % of the mean; in plain order one carries 20 % more.
+template <int N1>
+__device__ inline int wave_role() {
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
+  return N1 == 5 ? int(0xAB7298654310ull >> (4 * w)) & 15 : w;
+}
+// f(integral_constant PRM) for a Prandtl mode known at run time: only the
+// coefficient waves depend on it, so the kernel is not instantiated per mode.
+template <class F>
+__device__ inline void with_pr_mode(int prm, F&& f) {
+  if (prm == PR_UNIT) f(std::integral_constant<int, PR_UNIT>());
+  else if (prm == PR_LOW) f(std::integral_constant<int, PR_LOW>());
+  else f(std::integral_constant<int, PR_HIGH>());
+}
+template <int SPLIT, class S, int BCX, int BCY>
+__global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(planes_wpe<S>()))) void
+k_collide_advect_planes(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst, KParams kp,
+                        const typename S::T* __restrict__ ghost, int nstrips, int nranges, int prm) {
+  constexpr int N1 = Set<SPLIT>::N1;
+  __shared__ PlanesShared<SPLIT, typename S::C> sh;
+  int strip, ya, yb;
+  strip_range(kp.ny, nstrips, nranges, int(blockIdx.x), strip, ya, yb);
   const int x0 = strip * SWEEP_OWN;
-  // Role of the wave: plane waves of f (a), of g (N1 + a), coefficients of f
-  // and g.  With N1 = 5 the waves of one SIMD (every fourth) get f 0, g 0, f 2;
-  // f 1, g 1, g 2; f 3, g 3 and g's coefficients; f 4, g 4 and f's: with the
-  // planes of xi = 0 (no x flux) and the coefficients spread, the four carry
-  // within 6 % of the mean; in plain order one carries 20 % more.
-  int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
-  if (N1 == 5) w = int(0xAB7298654310ull >> (4 * w)) & 15;
+  const int w = wave_role<N1>();
   if (w < N1)
     planes_walk<SPLIT, S, BCX, BCY, 0>(src, dst, kp, w, x0, ya, yb, ghost, sh);
   else if (w < 2 * N1)
     planes_walk<SPLIT, S, BCX, BCY, 1>(src, dst, kp, w - N1, x0, ya, yb, ghost, sh);
   else if (w == 2 * N1)
-    planes_coeffs<SPLIT, S, PRM, 0>(kp, yb - ya, sh);
+    with_pr_mode(prm, [&](auto m) { planes_coeffs<SPLIT, S, decltype(m)::value, 0>(kp, yb - ya, sh); });
   else
-    planes_coeffs<SPLIT, S, PRM, 1>(kp, yb - ya, sh);
+    with_pr_mode(prm, [&](auto m) { planes_coeffs<SPLIT, S, decltype(m)::value, 1>(kp, yb - ya, sh); });
 }
 
 // Row range j of kseg in a column of ny rows for the column sweep: ranges of
@@ -515,6 +534,90 @@ __global__ __launch_bounds__(256) void k_adjoint_flux(const typename S::T* __res
     sweep_adjoint_flux<SPLIT, S, BCX, BCY, 1, LT>(state, lam1, work, lam0, kp, g - N1, strip * ADJ_STRIP, ya, yb);
 }
 
+// Adjoint step in one sweep: workgroup b is logical (strip, row range) first + b, dealt as
+// in the plane-group step kernel, with the same roles of the waves.  When
+// dparams != NULL the two coefficient waves of every workgroup leave their
+// sums of (d/dtau_ref, d/dPr) in partials[2 (2 b + k)], and the last wave to
+// finish (counted in *ticket, which it resets) adds them, in that order, to
+// dparams.
+// Against the two kernels it replaces (a relaxation kernel per cell that wrote
+// the moment cotangents to memory, and a flux sweep that read X, lam' and
+// them again: 2570 bytes per cell in float64), X and lam' are read and lam is written
+// once: 1200 bytes per cell plus the ranges' edge rows.  us per step, before /
+// after: float64 64^2 26.7 / 13.0, 256^2 46.2 / 29.6, 1024^2 639 / 284
+// (4.8 TB/s with the edges, of 5.7 for a copy); 16 populations 1024^2
+// 465 / 190; float32, float32 cotangents 2048^2 1596 / 848.
+// At 256^2 the edges count: 9 rows are read for 5 written.
+template <int SPLIT, class S, int BCX, int BCY, class LT>
+__global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(3))) void k_adjoint(
+    const typename S::T* __restrict__ state, const LT* __restrict__ lam1, LT* __restrict__ lam0, KParams kp,
+    int nstrips, int nranges, int first, int prm, double tau_ref, double* partials,
+    unsigned* ticket, double* dparams) {
+  constexpr int N1 = Set<SPLIT>::N1;
+  __shared__ AdjointShared<SPLIT> sh;
+  int strip, ya, yb;
+  strip_range(kp.ny, nstrips, nranges, first + int(blockIdx.x), strip, ya, yb);
+  const int x0 = strip * SWEEP_OWN, w = wave_role<N1>();
+  const auto walk = [&](auto d, int a) {
+    constexpr int D = decltype(d)::value;
+    if (N1 == 4 || a != N1 / 2) adjoint_walk<SPLIT, S, BCX, BCY, D, true, LT>(state, lam1, lam0, kp, a, x0, ya, yb, sh);
+    else adjoint_walk<SPLIT, S, BCX, BCY, D, false, LT>(state, lam1, lam0, kp, a, x0, ya, yb, sh);
+  };
+  if (w < N1) {
+    walk(std::integral_constant<int, 0>(), w);
+  } else if (w < 2 * N1) {
+    walk(std::integral_constant<int, 1>(), w - N1);
+  } else {
+    const int k = w - 2 * N1, lane = int(threadIdx.x & 63);
+    double acc[2] = {0.0, 0.0};
+    __builtin_amdgcn_s_setprio(2);
+    with_pr_mode(prm, [&](auto m) {
+      adjoint_coeffs<SPLIT, decltype(m)::value>(kp, k, x0, ya, yb, tau_ref, sh, acc[0], acc[1]);
+    });
+    if (!dparams) return;
+    auto wave_sum = [&](double v) {
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+      return v;
+    };
+    const int n = 2 * int(gridDim.x), slot = 2 * int(blockIdx.x) + k;
+    acc[0] = wave_sum(acc[0]);
+    acc[1] = wave_sum(acc[1]);
+    // The sums are stored and read at device scope, so the count needs only
+    // their completion before it; a __threadfence would write every dirty line
+    // of the L2 back first (256^2: 45 us with it, 28 us without).
+    unsigned before = 0;
+    if (lane == 0) {
+      __hip_atomic_store(partials + 2 * slot, acc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(partials + 2 * slot + 1, acc[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(int(before)) != n - 1) return;
+    asm volatile("" ::: "memory");
+    const double d0 = dparams[0], d1 = dparams[1];
+    double v[2] = {0.0, 0.0};
+    for (int b0 = lane; b0 < n; b0 += 64 * 8) {  // eight loads in flight at a time
+      double t[8][2];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        for (int j = 0; j < 2; ++j) {
+          const int b = b0 + 64 * u;
+          t[u][j] = __hip_atomic_load(partials + 2 * (b < n ? b : n - 1) + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        for (int j = 0; j < 2; ++j) v[j] += b0 + 64 * u < n ? t[u][j] : 0.0;
+    }
+    v[0] = wave_sum(v[0]);
+    v[1] = wave_sum(v[1]);
+    if (lane == 0) {
+      dparams[0] = d0 + v[0];
+      dparams[1] = d1 + v[1];
+      *ticket = 0u;
+    }
+  }
+}
+
 template <int SPLIT, class S>
 __global__ __launch_bounds__(256) void k_adjoint_readout(const typename S::T* __restrict__ state,
                                                          const double* rb, const double* uxb, const double* uyb,
@@ -740,7 +843,8 @@ struct dvbm_handle {
   hipStream_t stream;
   double dt;
   mutable int sweep_kseg;  // row ranges per strip of the column-sweep kernel (0: not chosen yet)
-  mutable int planes_ranges;  // the same of the plane-group kernel
+  mutable int planes_ranges;   // the same of the plane-group kernel
+  mutable int adjoint_ranges;  // and of the adjoint kernel
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -821,6 +925,28 @@ int planes_ranges(const void* kern, int block, int nstrips, int ny) {
   return n < 1 ? 1 : (n > ny ? ny : n);
 }
 
+// Row ranges per strip of the adjoint kernel: the number of rounds of
+// workgroups (1 to 4) with the least rows in sequence, a range costing about
+// five row steps besides its own rows.  One round is best where the strips
+// divide the device well (float64 1024^2, 18 strips: 284 us in one round of
+// 14 ranges, 325 us in two), several where they don't (4096^2, 69 strips:
+// three ranges fill 207 of 256 CUs, eleven 253 of them three times).
+int adjoint_ranges(const void* kern, int block, int nstrips, int ny) {
+  int ncu, per_cu, best = 1;
+  device_slots(kern, block, ncu, per_cu);
+  int64_t least = INT64_MAX;
+  for (int rounds = 1; rounds <= 4; ++rounds) {
+    int n = rounds * ncu * per_cu / nstrips;
+    n = n < 1 ? 1 : (n > ny ? ny : n);
+    const int64_t rows = int64_t(rounds) * ((ny + n - 1) / n + 5);
+    if (rows < least) {
+      least = rows;
+      best = n;
+    }
+  }
+  return best;
+}
+
 // Row ranges per strip group for the column sweep.  One workgroup fits a
 // CU at a time, so one round of ranges (as many workgroups as the device
 // holds) ends with its slowest CU; `rounds` rounds of shorter ranges let the
@@ -866,25 +992,10 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
   const T* s = static_cast<const T*>(src);
   T* d = static_cast<T*>(dst);
   const int kern_id = step_kernel(h);
-  T* gh = nullptr;
-  if constexpr (BCY == BC_WALL) {
-    gh = reinterpret_cast<T*>(h->ws + WS_GHOST);
-    hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream, s, gh,
-                       h->kp);
-  }
-  if (kern_id == KERNEL_PLANES) {
-    const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY, PRM>;
-    const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
-    if (h->planes_ranges == 0)
-      h->planes_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
-    hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->planes_ranges)), dim3(planes_threads<SPLIT>()), 0,
-                       h->stream, s, d, h->kp, static_cast<const T*>(gh), nstrips, h->planes_ranges);
-    return;
-  }
   if constexpr (BCY == BC_WALL) {
     const dim3 grid(((h->p.nx + CELL_TX - 1) / CELL_TX) * ((h->p.ny + CELL_TY - 1) / CELL_TY));
     hipLaunchKernelGGL((k_collide_advect<SPLIT, S, BCX, BCY, PRM>), grid, dim3(CELL_TX, CELL_TY), 0, h->stream, s, d,
-                       h->kp, static_cast<const T*>(gh));
+                       h->kp, reinterpret_cast<const T*>(h->ws + WS_GHOST));
     return;
   } else {
   if (kern_id == DVBM_KERNEL_TILE) {
@@ -918,7 +1029,21 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
 
 template <int SPLIT, class S, int BCX, int BCY>
 void launch_step_bc(const dvbm_handle* h, const void* src, void* dst) {
+  using T = typename S::T;
   const int prm = pr_mode(h->p.Pr);
+  if constexpr (BCY == BC_WALL)
+    hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream,
+                       static_cast<const T*>(src), reinterpret_cast<T*>(h->ws + WS_GHOST), h->kp);
+  if (step_kernel(h) == KERNEL_PLANES) {
+    const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
+    const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
+    if (h->planes_ranges == 0)
+      h->planes_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
+    hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->planes_ranges)), dim3(planes_threads<SPLIT>()), 0,
+                       h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp,
+                       reinterpret_cast<const T*>(h->ws + WS_GHOST), nstrips, h->planes_ranges, prm);
+    return;
+  }
   if (prm == PR_UNIT)
     launch_step_pr<SPLIT, S, BCX, BCY, PR_UNIT>(h, src, dst);
   else if (prm == PR_LOW)
@@ -946,15 +1071,13 @@ void step(const dvbm_handle* h, const void* src, void* dst) {
 }
 
 template <int SPLIT, class S, int BCX, int BCY, class LT>
-void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work,
-                double* ws);
+void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work, double* ws);
 
 // Cotangents lam1, lam0 stored as LT (double or float); the arithmetic and the
-// work array are float64.  ws: the reduction area (block partials of
+// work array (of the deviation storage) are float64.  ws: the reduction area (block partials of
 // d/dtau_ref, d/dPr from offset 0, the block counter at WS_TICKET doubles).
 template <int SPLIT, class S, class LT>
-void adjoint(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work,
-             double* ws) {
+void adjoint(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work, double* ws) {
   const int bx = h->p.bc_x, by = h->p.bc_y;
   if (bx == DVBM_PERIODIC && by == DVBM_PERIODIC)
     adjoint_bc<SPLIT, S, BC_PERIODIC, BC_PERIODIC, LT>(h, state, lam1, lam0, dparams, work, ws);
@@ -967,35 +1090,48 @@ void adjoint(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, 
 }
 
 template <int SPLIT, class S, int BCX, int BCY, class LT>
-void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work,
-                double* ws) {
-  using T = typename S::T;
-  const T* s = static_cast<const T*>(state);
-  const double tau = h->p.tau_ref;
-  unsigned* ticket = reinterpret_cast<unsigned*>(ws + WS_TICKET);
-  const int64_t cells = int64_t(h->p.nx) * h->p.ny;
-  const int64_t nb = (cells + RED_THREADS - 1) / RED_THREADS;
-  const dim3 grid(unsigned(nb < ADJ_RELAX_BLOCKS ? nb : ADJ_RELAX_BLOCKS)), block(RED_THREADS);
-  switch (pr_mode(h->p.Pr)) {
-    case PR_UNIT:
-      hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_UNIT, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                         ws, ticket, dparams);
-      break;
-    case PR_LOW:
-      hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_LOW, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                         ws, ticket, dparams);
-      break;
-    default:
-      hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_HIGH, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                         ws, ticket, dparams);
-      break;
+void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work, double* ws) {
+  if constexpr (!S::dev) {
+    const auto kern = k_adjoint<SPLIT, S, BCX, BCY, LT>;
+    const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
+    if (h->adjoint_ranges == 0)
+      h->adjoint_ranges = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
+    const int nr = h->adjoint_ranges, total = nstrips * nr;
+    // more strips than the workspace has partials for: in turns
+    for (int first = 0; first < total; first += ADJ_BLOCKS)
+      hipLaunchKernelGGL(kern, dim3(unsigned(total - first < ADJ_BLOCKS ? total - first : ADJ_BLOCKS)),
+                         dim3(planes_threads<SPLIT>()), 0, h->stream, static_cast<const typename S::T*>(state), lam1,
+                         lam0, h->kp, nstrips, nr, first, pr_mode(h->p.Pr), h->p.tau_ref, ws,
+                         reinterpret_cast<unsigned*>(ws + WS_TICKET), dparams);
+  } else {
+    using T = typename S::T;
+    const T* s = static_cast<const T*>(state);
+    const double tau = h->p.tau_ref;
+    unsigned* ticket = reinterpret_cast<unsigned*>(ws + WS_TICKET);
+    const int64_t cells = int64_t(h->p.nx) * h->p.ny;
+    const int64_t nb = (cells + RED_THREADS - 1) / RED_THREADS;
+    const dim3 grid(unsigned(nb < ADJ_RELAX_BLOCKS ? nb : ADJ_RELAX_BLOCKS)), block(RED_THREADS);
+    switch (pr_mode(h->p.Pr)) {
+      case PR_UNIT:
+        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_UNIT, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
+                           ws, ticket, dparams);
+        break;
+      case PR_LOW:
+        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_LOW, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
+                           ws, ticket, dparams);
+        break;
+      default:
+        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_HIGH, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
+                           ws, ticket, dparams);
+        break;
+    }
+    const int64_t groups = 2 * Set<SPLIT>::N1, nstrips = (h->p.nx + ADJ_STRIP - 1) / ADJ_STRIP;
+    int64_t ch = (int64_t(h->p.ny) * groups * nstrips + DVBM_ADJ_WAVES - 1) / DVBM_ADJ_WAVES;
+    ch = ch < DVBM_ADJ_CH_MIN ? DVBM_ADJ_CH_MIN : (ch > h->p.ny ? h->p.ny : ch);
+    const int64_t nchunks = (h->p.ny + ch - 1) / ch, waves = groups * nstrips * nchunks;
+    hipLaunchKernelGGL((k_adjoint_flux<SPLIT, S, BCX, BCY, LT>), dim3(unsigned((waves + 3) / 4)), dim3(256), 0, h->stream,
+                       s, lam1, work, lam0, h->kp, int(nstrips), int(ch), int(nchunks));
   }
-  const int64_t groups = 2 * Set<SPLIT>::N1, nstrips = (h->p.nx + ADJ_STRIP - 1) / ADJ_STRIP;
-  int64_t ch = (int64_t(h->p.ny) * groups * nstrips + DVBM_ADJ_WAVES - 1) / DVBM_ADJ_WAVES;
-  ch = ch < DVBM_ADJ_CH_MIN ? DVBM_ADJ_CH_MIN : (ch > h->p.ny ? h->p.ny : ch);
-  const int64_t nchunks = (h->p.ny + ch - 1) / ch, waves = groups * nstrips * nchunks;
-  hipLaunchKernelGGL((k_adjoint_flux<SPLIT, S, BCX, BCY, LT>), dim3(unsigned((waves + 3) / 4)), dim3(256), 0, h->stream,
-                     s, lam1, work, lam0, h->kp, int(nstrips), int(ch), int(nchunks));
 }
 
 }  // namespace dvbm_launch
@@ -1142,8 +1278,7 @@ struct EncodeOp {
 template <int SPLIT, class S>
 struct AdjointOp {
   template <class LT>
-  static void run(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams,
-                  double* work, double* ws) {
+  static void run(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work, double* ws) {
     dvbm_launch::adjoint<SPLIT, S, LT>(h, state, lam1, lam0, dparams, work, ws);
   }
 };
@@ -1293,6 +1428,7 @@ int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const d
   h->stream = s;
   h->sweep_kseg = 0;
   h->planes_ranges = 0;
+  h->adjoint_ranges = 0;
   // the fixed scratch of dvbm_adjoint_step_noalloc on this device (set-up only:
   // that entry point then makes no runtime call besides its launches)
   h->scratch = nullptr;
@@ -1391,9 +1527,9 @@ static int adjoint_storage_ok(const dvbm_handle* h, const char* who) {
   if (h->p.storage != DVBM_F64 && h->p.storage != DVBM_F32 && h->p.storage != DVBM_F32_DEV)
     return fail(DVBM_EINVAL, std::string(who) + ": the adjoint supports f64, f32 and f32_dev storage");
   if (h->p.bc_y == DVBM_WALL) return fail(DVBM_EINVAL, std::string(who) + ": the adjoint does not support walls");
-  // the flux adjoint stores each cotangent plane through one buffer resource
-  // with 32-bit offsets and discards stores at offset 2^31 (the distribution
-  // limit keeps a float64 plane below 0.6 GiB)
+  // the adjoint addresses a cotangent plane, or a row of N1 planes, through one
+  // buffer resource with 32-bit offsets and discards stores at offset 2^31
+  // (the distribution limit keeps N1 float64 planes below that)
   if (int64_t(h->p.nx) * h->p.ny * int64_t(sizeof(double)) >= (int64_t(1) << 31))
     return fail(DVBM_EINVAL, std::string(who) + ": a cotangent plane must stay below 2 GiB");
   return DVBM_OK;

@@ -238,7 +238,7 @@ __device__ inline void fold_columns(F&& col, double* out) {
     col(a, s0, s1, s2, s3);
     acc[0] = w * s0;
     acc[2] = w * s1;
-    if (D == 0) {
+    if constexpr (D == 0) {
       acc[5] = w * s2;
       acc[9] = w * s3;
     }
@@ -254,7 +254,7 @@ __device__ inline void fold_columns(F&& col, double* out) {
     acc[0] += w * e0;
     acc[1] += (w * x) * o0;
     acc[2] += w * e1;
-    if (D == 0) {
+    if constexpr (D == 0) {
       const double o1 = a1 - b1, e2 = a2 + b2, o2 = a2 - b2;
       acc[3] += (w * x * x) * e0;
       acc[4] += (w * x) * o1;

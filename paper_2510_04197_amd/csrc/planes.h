@@ -19,7 +19,7 @@
 //   float64  64^2 6.0 (19.3), 256^2 15.0 (23.9), 512^2 39 (58)
 //   float64, 16 populations, 512 x 4  4.9 (13.6)
 //   float32 deviations  64^2 4.4 (9.3), 256^2 9.0 (11.8), 512^2 21.8 (30.5)
-//   float16 deviations, 16 populations, 509 x 383  12.7 (17.1)
+//   float16 deviations, 16 populations, 509 x 383  12.2 (17.1)
 #pragma once
 
 #include "step.h"
@@ -49,6 +49,21 @@ __device__ inline double uniform(double v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(int(uint32_t(b)));
   const uint32_t hi = __builtin_amdgcn_readfirstlane(int(uint32_t(b >> 32)));
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+}
+
+// Keeps the value's computation at this place: values carried from row to row
+// would otherwise be sunk into the next row step, with everything they are
+// computed from.
+template <class R>
+__device__ inline void here(R& v) { asm volatile("" : "+v"(v)); }
+// An LDS address that the accesses at constant offsets share (beyond the first
+// 64 KiB of a block each access gets an address register of its own otherwise).
+template <class P>
+__device__ inline P* lds_base(P* p) {
+  using Q = __attribute__((address_space(3))) P*;
+  Q q = (Q)p;
+  asm volatile("" : "+v"(q));
+  return (P*)q;
 }
 
 // Moments of one cell (lane) from the columns' sums, and the collision
@@ -102,7 +117,7 @@ constexpr int PLANES_RING = 4;
 // otherwise; at phase P = (y - ya) % ring it is in register (P + r) % ring.
 // A row is requested when the window drops one, and decoded at its first use.
 template <int SPLIT, class S, int BCX, int BCY, int D>
-__device__ inline void planes_walk(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst,
+__device__ __attribute__((always_inline)) inline void planes_walk(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst,
                                    const KParams& kp, int a, int x0, int ya, int yb,
                                    const typename S::T* __restrict__ ghost,
                                    PlanesShared<SPLIT, typename S::C>& sh) {
@@ -254,20 +269,19 @@ __device__ inline void planes_walk(const typename S::T* __restrict__ src, typena
         const double h = (S::dev ? 1.0 : L::w(b)) * hn(q, xb);
         if (h != 0.0) xn += R(h) * e[q];
       }
-      R div = R(0);
       if constexpr (MOV) {
         const R d = c0 - lane_prev(c0);
         const R fr = c0 + R(0.25) * lim4(d, lane_next(d), beta2);  // face downwind
-        div = kvx * (fr - lane_prev(fr));
+        xn -= kvx * (fr - lane_prev(fr));
       }
       if (xb != 0.0) {
         if (xb < 0.0) wn[(P + 2) % RG] = Bits<T>::decode(wn[(P + 2) % RG]);
         const R r0 = wn[P], r1 = wn[(P + 1) % RG], r2 = wn[(P + 2) % RG];
         const R fa = xb > 0.0 ? face(r0, r1, r2) : face(r2, r1, r0);
-        div += kvy[b] * (fa - fbelow[b]);
+        xn -= kvy[b] * (fa - fbelow[b]);
         fbelow[b] = fa;
       }
-      const R xnew = c0 + (xn - div);
+      const R xnew = c0 + xn;
       T out;
       if constexpr (S::dev) out = S::enc_dev(xnew);
       else out = S::enc(xnew, R(1), R(0));
@@ -293,7 +307,7 @@ __device__ inline void planes_walk(const typename S::T* __restrict__ src, typena
 }
 
 template <int SPLIT, class S, int PRM, int D>
-__device__ inline void planes_coeffs(const KParams& kp, int n, PlanesShared<SPLIT, typename S::C>& sh) {
+__device__ __attribute__((always_inline)) inline void planes_coeffs(const KParams& kp, int n, PlanesShared<SPLIT, typename S::C>& sh) {
   const int lane = threadIdx.x & 63;
   for (int k = 0; k < n; ++k) {
     __syncthreads();

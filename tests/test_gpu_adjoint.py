@@ -97,6 +97,17 @@ def test_step_adjoint_grid_shapes(shape, bc):
     check_step_adjoint(step_adjoint_vs_oracle(shape[0], shape[1], 2, 0.71, bc[0], bc[1], "f64", seed=3))
 
 
+@pytest.mark.parametrize("shape", ((59, 6), (60, 4), (61, 5), (63, 7), (64, 300), (121, 40), (20, 3000), (61500, 4)),
+                         ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("bc,split", ((BCS[0], 2), (BCS[3], 2), (BCS[3], 1)), ids=("pp-2", "zz-2", "zz-1"))
+def test_step_adjoint_strips_and_row_ranges(shape, bc, split):
+    # strips of 60 columns with one owned column or none to spare, grids around the one-wrap width of 64 columns,
+    # one row per range, ranges of unequal length, and 1025 strips (two launches: the workspace holds the
+    # parameter sums of 1024 workgroups); float64, whose random states meet no kink of the limiter (float32 values
+    # do on grids of this size, where the oracle's reverse mode takes another subgradient)
+    check_step_adjoint(step_adjoint_vs_oracle(shape[0], shape[1], split, 0.71, bc[0], bc[1], "f64", seed=5))
+
+
 @pytest.mark.parametrize("storage,nx,ny,bc_x", (("f64", 4096, 4096, "periodic"), ("f32_dev", 4099, 2053, "periodic"),
                                                  ("f32", 2048, 1024, "zero_gradient")))
 def test_step_adjoint_full_size_sampled(storage, nx, ny, bc_x):
