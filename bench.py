@@ -76,9 +76,12 @@ def traffic_entry(kernel_key: str):
 
 
 def step_kernel_name(storage: str, wl) -> str:
-    """The step kernel of a workload here: what AUTO launches on grids of at least 3 * 2^18 cells;
+    """The step kernel of a workload here: what AUTO launches on grids of at least 3 * 2^18 cells (split II);
     below that the storage's one-thread-per-cell kernel (``kernel="tile"`` or ``"cell"``), where
     AUTO takes the plane-group kernel instead."""
+    cells = wl.nx * wl.ny
+    if 3 << 18 <= cells < {8: 15 << 16, 4: 7 << 17, 2: 9 << 17}[STORAGE_BYTES[storage]]:
+        return "k_collide_advect_planes"
     big = wl.nx * wl.ny >= 3 << 18
     if storage == "f64":
         return "k_collide_advect_sweep" if big else "k_collide_advect_lds"

@@ -197,11 +197,19 @@ __device__ inline void sweep_range(int ny, int kseg, int j, int u, int& ya, int&
 #define DVBM_SWEEP_WPE 2
 #endif
 // Below this many cells a grid has too few strip groups x row ranges to
-// occupy the device, and the plane-group kernel is faster: us per step,
-// planes / sweep, float64 512^2 39 / 60, 800^2 124 / 125; float32 deviations
-// 512^2 21.8 / 44, 800^2 54.9 / 54.0; and above it float64 1024^2 192 / 196,
-// float32 1024^2 113 / 105, 4096^2 1590 / 1446.
-constexpr int64_t SWEEP_MIN_CELLS = 3 << 18;
+// occupy the device with the column sweep, and the plane-group kernel is
+// faster.  us per step, planes / sweep:
+//   25 populations  float64 900^2 155 / 162, 1024^2 197 / 197, 3001 x 1499 821 / 795;
+//                   32-bit 900^2 83.7 / 85.8, 1024^2 115 / 100, 4096^2 1590 / 1446;
+//                   16-bit 1024^2 64.6 / 70.4, 1500 x 1100 117 / 115
+//   16 populations  float64 1024^2 119 / 122, 2048^2 472 / 498, 4096^2 1757 / 1943 (two workgroups per CU fit);
+//                   32-bit 1500 x 1000 99.6 / 104, 2048 x 1024 137 / 124;
+//                   16-bit 2048 x 1024 87 / 97, 2048^2 181 / 183
+template <int SPLIT>
+__host__ constexpr int64_t sweep_min_cells(int bytes) {
+  return SPLIT == 2 ? (bytes == 8 ? 15 << 16 : bytes == 4 ? 7 << 17 : 9 << 17)
+                    : (bytes == 8 ? INT64_MAX : bytes == 4 ? 3 << 19 : 1 << 22);
+}
 #ifndef DVBM_SWEEP_K64
 #define DVBM_SWEEP_K64 2  // strips per workgroup, float64 storage
 #endif
@@ -912,16 +920,19 @@ void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
 // they fit and leave ranges of at least 4 rows (f32_dev, 256^2: 8.95 us with
 // 255 ranges of 5 rows, 9.55 us with 510 of 2.5; 512^2: 22.8 us with 252,
 // 21.8 us with 504; three per CU, split I: 14.3 us against 12.7 us at 509 x 383).
-// Ranges that would be longer than 32 rows are cut to 16, in more rounds:
-// neighbouring workgroups then stay close in memory (float64 1024^2: 206 us in
-// one round of 68 rows, 192 us at 9 rows; f32 4096^2: 1590 us at 8 to 16 rows,
-// 1790 us at 32).
+// Ranges that would be longer than 32 rows are cut to 16 or less, in as many
+// full rounds: neighbouring workgroups then stay close in memory (float64
+// 1024^2: 206 us in one round of 68 rows, 192 us in seven of 9; f32 4096^2:
+// 1590 us at 8 to 16 rows, 1790 us at 32).
 int planes_ranges(const void* kern, int block, int nstrips, int ny) {
   int ncu, per_cu;
   device_slots(kern, block, ncu, per_cu);
   int n = per_cu >= 2 ? 2 * ncu / nstrips : 0;
   if (n < 1 || ny / n < 4) n = ncu / nstrips;
-  if (n < 1 || ny / n > 32) n = ny / 16;
+  if (n < 1 || ny / n > 32) {
+    const int64_t slots = int64_t(ncu) * per_cu, rounds = (int64_t(nstrips) * ny + 16 * slots - 1) / (16 * slots);
+    n = int(rounds * slots / nstrips);
+  }
   return n < 1 ? 1 : (n > ny ? ny : n);
 }
 
@@ -963,9 +974,24 @@ int sweep_ranges(const void* kern, int block, int ngroups, int ny, int rounds, i
   if (want < one) want = one;
   if (want > ny / (3 * unit)) want = ny / (3 * unit);
   if (want < 1) want = 1;
-  // the number of ranges of sweep_len rows that cover the column
-  const int len = sweep_len(ny, want, unit);
-  return (ny + len - 1) / len;
+  // the number of ranges of sweep_len rows that cover the column; fewer, longer
+  // ones where the last round would leave more than a tenth of the slots idle
+  // (float64 3001 x 1499, 26 groups on 256 CUs: 30 ranges take four rounds,
+  // the last nearly empty, 967 us; 28 take three, 812 us)
+  const int slots = ncu * per_cu;
+  int best = 0;
+  double full = 0.0;
+  for (int w = want; w >= 1 && 2 * w >= want; --w) {
+    const int len = sweep_len(ny, w, unit), n = (ny + len - 1) / len;
+    const int64_t groups = int64_t(n) * ngroups, rounds_up = (groups + slots - 1) / slots;
+    const double f = double(groups) / double(rounds_up * slots);
+    if (f > full + 1e-9) {
+      full = f;
+      best = n;
+    }
+    if (full >= 0.9) break;
+  }
+  return best;
 }
 
 }  // namespace
@@ -977,9 +1003,10 @@ namespace dvbm_launch {
 
 // The kernel a handle's steps use (the AUTO rule of dvbm_kernel).
 constexpr int KERNEL_PLANES = -1;  // the plane-group kernel: chosen by AUTO only
-inline int step_kernel(const dvbm_handle* h) {
+template <int SPLIT>
+int step_kernel(const dvbm_handle* h) {
   if (h->p.kernel != DVBM_KERNEL_AUTO) return h->p.kernel;
-  const bool big = int64_t(h->p.nx) * h->p.ny >= SWEEP_MIN_CELLS;
+  const bool big = int64_t(h->p.nx) * h->p.ny >= sweep_min_cells<SPLIT>(storage_bytes(h->p.storage));
   if (h->p.bc_y == DVBM_WALL || !big) return KERNEL_PLANES;
   if (h->p.storage == DVBM_F64) return DVBM_KERNEL_SWEEP;
   const uint64_t dist = uint64_t(h->kp.sdist) * uint64_t(storage_bytes(h->p.storage));
@@ -991,7 +1018,7 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
   using T = typename S::T;
   const T* s = static_cast<const T*>(src);
   T* d = static_cast<T*>(dst);
-  const int kern_id = step_kernel(h);
+  const int kern_id = step_kernel<SPLIT>(h);
   if constexpr (BCY == BC_WALL) {
     const dim3 grid(((h->p.nx + CELL_TX - 1) / CELL_TX) * ((h->p.ny + CELL_TY - 1) / CELL_TY));
     hipLaunchKernelGGL((k_collide_advect<SPLIT, S, BCX, BCY, PRM>), grid, dim3(CELL_TX, CELL_TY), 0, h->stream, s, d,
@@ -1034,7 +1061,7 @@ void launch_step_bc(const dvbm_handle* h, const void* src, void* dst) {
   if constexpr (BCY == BC_WALL)
     hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream,
                        static_cast<const T*>(src), reinterpret_cast<T*>(h->ws + WS_GHOST), h->kp);
-  if (step_kernel(h) == KERNEL_PLANES) {
+  if (step_kernel<SPLIT>(h) == KERNEL_PLANES) {
     const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
     if (h->planes_ranges == 0)

@@ -170,7 +170,7 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
   auto load = [&](const Row& r, int b, uint32_t lo) -> R {
     return Bits<T>::keep(Buf<T>::ld(r.r, r.so + uint32_t(b) * r.stride, lo));
   };
-  auto face = [&](R u, R c, R n) -> R { return c + R(0.25) * lim4(c - u, n - c, beta2); };
+  auto face = [&](R u, R c, R n) -> R { return add_quarter(c, lim4_walk(c - u, n - c, beta2)); };
 
   R win[N1][RG], fbelow[N1];
   {
@@ -271,7 +271,7 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
       }
       if constexpr (MOV) {
         const R d = c0 - lane_prev(c0);
-        const R fr = c0 + R(0.25) * lim4(d, lane_next(d), beta2);  // face downwind
+        const R fr = add_quarter(c0, lim4_walk(d, lane_next(d), beta2));  // face downwind
         xn -= kvx * (fr - lane_prev(fr));
       }
       if (xb != 0.0) {

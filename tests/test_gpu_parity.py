@@ -508,6 +508,17 @@ def test_thermal_wave_4096_sampled_16bit(storage, u):
     assert e <= 1.5 * u * dev
 
 
+@pytest.mark.parametrize("split,storage,nx,ny", ((2, "f64", 3001, 1499), (1, "f64", 2048, 1025), (2, "f32", 900, 901),
+                                                 (1, "f32_dev", 1400, 1000)))
+def test_kernel_choice_sampled(split, storage, nx, ny):
+    """Grids around AUTO's lines: the column sweep with fewer ranges than it aims for, so that the last round of
+    workgroups is full, and the plane-group kernel in several rounds; one step on sampled cells."""
+    wl = smooth_random(nx, ny, seed=24, amp_T=0.05)
+    s, p = solver(wl, split=split, storage=storage, Pr=0.71, tau_ref=5e-5)
+    got, ref, before = sampled_check(s, p, nsamples=48, seed=8)
+    check_sampled(got, ref, before, storage, 1e-12 if storage == "f64" else 1e-5, f"{nx}x{ny} {storage}")
+
+
 def test_largest_grids_sampled():
     """6528 x 6528, split II.  In float32 one distribution takes 3.97 GiB: the
     32-bit buffer offsets are near their 4 GiB limit, and the grid is above the
