@@ -152,21 +152,29 @@ __device__ inline void with_pr_mode(int prm, F&& f) {
 template <int SPLIT, class S, int BCX, int BCY>
 __global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(planes_wpe<S>()))) void
 k_collide_advect_planes(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst, KParams kp,
-                        const typename S::T* __restrict__ ghost, int nstrips, int nranges, int prm) {
+                        int nstrips, int nranges, int prm) {
   constexpr int N1 = Set<SPLIT>::N1;
-  __shared__ PlanesShared<SPLIT, typename S::C> sh;
+  __shared__ PlanesShared<SPLIT, typename S::C, BCY == BC_WALL> sh;
   int strip, ya, yb;
   strip_range(kp.ny, nstrips, nranges, int(blockIdx.x), strip, ya, yb);
   const int x0 = strip * SWEEP_OWN;
   const int w = wave_role<N1>();
+  const auto coeffs = [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    if constexpr (BCY == BC_WALL) {  // the ghost rows that this range reads
+      if (ya < 2) wall_coeffs<SPLIT, S, D>(kp, 0, sh);
+      if (yb > kp.ny - 2) wall_coeffs<SPLIT, S, D>(kp, 1, sh);
+    }
+    with_pr_mode(prm, [&](auto m) { planes_coeffs<SPLIT, S, decltype(m)::value, D>(kp, yb - ya, sh); });
+  };
   if (w < N1)
-    planes_walk<SPLIT, S, BCX, BCY, 0>(src, dst, kp, w, x0, ya, yb, ghost, sh);
+    planes_walk<SPLIT, S, BCX, BCY, 0>(src, dst, kp, w, x0, ya, yb, sh);
   else if (w < 2 * N1)
-    planes_walk<SPLIT, S, BCX, BCY, 1>(src, dst, kp, w - N1, x0, ya, yb, ghost, sh);
+    planes_walk<SPLIT, S, BCX, BCY, 1>(src, dst, kp, w - N1, x0, ya, yb, sh);
   else if (w == 2 * N1)
-    with_pr_mode(prm, [&](auto m) { planes_coeffs<SPLIT, S, decltype(m)::value, 0>(kp, yb - ya, sh); });
+    coeffs(std::integral_constant<int, 0>());
   else
-    with_pr_mode(prm, [&](auto m) { planes_coeffs<SPLIT, S, decltype(m)::value, 1>(kp, yb - ya, sh); });
+    coeffs(std::integral_constant<int, 1>());
 }
 
 // Row range j of kseg in a column of ny rows for the column sweep: ranges of
@@ -318,7 +326,8 @@ __device__ inline double decode_one(const typename S::T v, int d, int i, const K
 // u_G = 2 u_W - u_B, T_G = 2 T_W - T_B) and the populations
 // X^eq(G) + (X_B - X^eq(B)), encoded in the storage format.
 // ghost[(d Q + i) 4 + r][x] (row stride pitch), r = 0..3 for the rows -2, -1,
-// ny, ny+1; one thread per (x, r).
+// ny, ny+1; one thread per (x, r).  For the per-cell kernel; the plane-group
+// kernel forms its ghost rows itself.
 template <int SPLIT, class S>
 __global__ __launch_bounds__(256) void k_wall_ghosts(const typename S::T* __restrict__ src,
                                                      typename S::T* __restrict__ ghost, KParams kp) {
@@ -1058,19 +1067,18 @@ template <int SPLIT, class S, int BCX, int BCY>
 void launch_step_bc(const dvbm_handle* h, const void* src, void* dst) {
   using T = typename S::T;
   const int prm = pr_mode(h->p.Pr);
-  if constexpr (BCY == BC_WALL)
-    hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream,
-                       static_cast<const T*>(src), reinterpret_cast<T*>(h->ws + WS_GHOST), h->kp);
   if (step_kernel<SPLIT>(h) == KERNEL_PLANES) {
     const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
     if (h->planes_ranges == 0)
       h->planes_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
     hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->planes_ranges)), dim3(planes_threads<SPLIT>()), 0,
-                       h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp,
-                       reinterpret_cast<const T*>(h->ws + WS_GHOST), nstrips, h->planes_ranges, prm);
+                       h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp, nstrips, h->planes_ranges, prm);
     return;
   }
+  if constexpr (BCY == BC_WALL)
+    hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream,
+                       static_cast<const T*>(src), reinterpret_cast<T*>(h->ws + WS_GHOST), h->kp);
   if (prm == PR_UNIT)
     launch_step_pr<SPLIT, S, BCX, BCY, PR_UNIT>(h, src, dst);
   else if (prm == PR_LOW)

@@ -20,6 +20,11 @@
 //   float64, 16 populations, 512 x 4  4.9 (13.6)
 //   float32 deviations  64^2 4.4 (9.3), 256^2 9.0 (11.8), 512^2 21.8 (30.5)
 //   float16 deviations, 16 populations, 509 x 383  12.2 (17.1)
+//   thermal Couette flow between walls, float64, 4 x 128  9.1 (38.6)
+// No-slip walls: a range next to a wall forms the ghost rows it reads itself,
+// by the same exchange (shares of the two mirrored rows, the difference of the
+// two equilibria's coefficients, expansion), two barriers per wall; a
+// kernel of its own for them took 4.6 us of the 13.4 us a step then took.
 #pragma once
 
 #include "step.h"
@@ -30,9 +35,19 @@ namespace dvbm {
 // Coefficients a_(p,q), p + q <= N, of one Grad expansion.
 constexpr int n_coeffs(int N) { return (N + 1) * (N + 2) / 2; }
 
+// With walls: by distance k from the wall, the ghost row's equilibrium
+// coefficients less those of the row it mirrors.
+template <int SPLIT, bool WALL>
+struct PlanesWall {};
+template <int SPLIT>
+struct PlanesWall<SPLIT, true> {
+  double wf[2][n_coeffs(Set<SPLIT>::NF)][64];
+  double wg[2][n_coeffs(Set<SPLIT>::NG)][64];
+};
+
 // Double-buffered by row parity.
-template <int SPLIT, class R>
-struct PlanesShared {
+template <int SPLIT, class R, bool WALL>
+struct PlanesShared : PlanesWall<SPLIT, WALL> {
   static constexpr int N1 = Set<SPLIT>::N1;
   double fsum[2][N1][4][64];                      // sums over b of xi_b^k f, k = 0..3, per column a
   double gsum[2][N1][2][64];                      // of xi_b^k g, k = 0, 1
@@ -66,14 +81,11 @@ __device__ inline P* lds_base(P* p) {
   return (P*)q;
 }
 
-// Moments of one cell (lane) from the columns' sums, and the collision
-// coefficients of distribution D, in the order p, q, then om1.
-template <int SPLIT, class S, int PRM, int D>
-__device__ inline void node_coeffs(const KParams& kp, const double (*fsum)[4][64], const double (*gsum)[2][64],
-                                   typename S::C (*out)[64], int lane) {
-  using R = typename S::C;
+// Moments of one cell (lane) from the columns' sums.
+template <int SPLIT, class S>
+__device__ inline NodeMoments lane_moments(const KParams& kp, const double (*fsum)[4][64], const double (*gsum)[2][64],
+                                           int lane) {
   constexpr int N1 = Set<SPLIT>::N1;
-  constexpr int N = D == 0 ? Set<SPLIT>::NF : Set<SPLIT>::NG;
   double mf[10], mg[3];
   fold_columns<0, N1, S::dev>(
       [&](int k, double& s0, double& s1, double& s2, double& s3) {
@@ -90,7 +102,16 @@ __device__ inline void node_coeffs(const KParams& kp, const double (*fsum)[4][64
         s2 = s3 = 0.0;
       },
       mg);
-  const NodeMoments m = S::dev ? add_rest_moments(mf, mg, kp) : as_moments(mf, mg);
+  return S::dev ? add_rest_moments(mf, mg, kp) : as_moments(mf, mg);
+}
+
+// The collision coefficients of distribution D in the order p, q, then om1.
+template <int SPLIT, class S, int PRM, int D>
+__device__ inline void node_coeffs(const KParams& kp, const double (*fsum)[4][64], const double (*gsum)[2][64],
+                                   typename S::C (*out)[64], int lane) {
+  using R = typename S::C;
+  constexpr int N = D == 0 ? Set<SPLIT>::NF : Set<SPLIT>::NG;
+  const NodeMoments m = lane_moments<SPLIT, S>(kp, fsum, gsum, lane);
   R bf[5][5], bg[3][3], om1;
   collision_coeffs<SPLIT, PRM, R>(m, kp, kp.om_scale, kp.Pr, bf, bg, om1);
   if constexpr (S::dev) subtract_rest<SPLIT>(bf, bg, om1, kp);
@@ -100,6 +121,64 @@ __device__ inline void node_coeffs(const KParams& kp, const double (*fsum)[4][64
 #pragma unroll
     for (int q = 0; p + q <= N; ++q, ++k) out[k][lane] = D == 0 ? bf[p][q] : bg[p][q];
   out[k][lane] = om1;
+}
+
+// Equilibrium coefficients of distribution D (order p, q) added to out with a
+// sign: rho, the normalised velocity and T (Sec. II D 2, Apps. A and D).
+template <int SPLIT, int D>
+__device__ inline void add_equilibrium_coeffs(double sign, double rho, double ux, double uy, double T,
+                                              const KParams& kp, double* out) {
+  constexpr int N = D == 0 ? Set<SPLIT>::NF : Set<SPLIT>::NG;
+  const double RT = kp.R * T, th = RT / kp.c2, p = rho * RT;
+  double mx[5], my[5];
+  gauss_hermite_moments(ux, th - 1.0, mx);
+  gauss_hermite_moments(uy, th - 1.0, my);
+  if (D == 0 || SPLIT == 2) {
+    const double w = sign * (D == 0 ? rho : rho * (kp.Cv - kp.R) * T);
+    int k = 0;
+#pragma unroll
+    for (int a = 0; a <= N; ++a)
+#pragma unroll
+      for (int b = 0; a + b <= N; ++b, ++k) out[k] += w * mx[a] * my[b];
+  } else {  // order (0,0) (0,1) (0,2) (1,0) (1,1) (2,0)
+    const double E = rho * kp.Cv * T + 0.5 * rho * kp.c2 * (ux * ux + uy * uy);
+    const double Ep = E + p, E2p = E + 2.0 * p, diag = Ep * th - E;
+    out[0] += sign * E;
+    out[1] += sign * uy * Ep;
+    out[2] += sign * (E2p * uy * uy + diag);
+    out[3] += sign * ux * Ep;
+    out[4] += sign * E2p * ux * uy;
+    out[5] += sign * (E2p * ux * ux + diag);
+  }
+}
+
+// No-slip wall w (0: below row 0, 1: above row ny - 1): from the shares of the
+// two rows next to it (slot k: k rows away), the coefficients X^eq(G) - X^eq(B)
+// of distribution D, with the ghost fields rho_G = rho_B, u_G = 2 u_W - u_B,
+// T_G = 2 T_W - T_B.
+template <int SPLIT, class S, int D, class SH>
+__device__ inline void wall_coeffs(const KParams& kp, int w, SH& sh) {
+  constexpr int M = n_coeffs(D == 0 ? Set<SPLIT>::NF : Set<SPLIT>::NG);
+  const int lane = threadIdx.x & 63;
+  __syncthreads();
+  for (int k = 0; k < 2; ++k) {
+    const NodeMoments m = lane_moments<SPLIT, S>(kp, sh.fsum[k], sh.gsum[k], lane);
+    const double irho = 1.0 / m.rho, ux = m.jx * irho, uy = m.jy * irho;
+    const double E = SPLIT == 2 ? m.g0 + 0.5 * kp.c2 * (m.pxx + m.pyy) : m.g0;
+    const double T = (E * irho - 0.5 * kp.c2 * (ux * ux + uy * uy)) * kp.inv_Cv;
+    double d[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) d[j] = 0.0;
+    add_equilibrium_coeffs<SPLIT, D>(1.0, m.rho, 2.0 * kp.wall_ux[w] / sqrt(kp.c2) - ux, -uy, 2.0 * kp.wall_T[w] - T,
+                                     kp, d);
+    add_equilibrium_coeffs<SPLIT, D>(-1.0, m.rho, ux, uy, T, kp, d);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      if constexpr (D == 0) sh.wf[k][j][lane] = d[j];
+      else sh.wg[k][j][lane] = d[j];
+    }
+  }
+  __syncthreads();
 }
 
 // Rows held per plane: the rows y-1 .. y+2 (xi_b > 0) or y .. y+3, the last one
@@ -116,15 +195,15 @@ constexpr int PLANES_RING = 4;
 // Window of plane (a, b): ring row r holds row y - 1 + r when xi_b > 0, y + r
 // otherwise; at phase P = (y - ya) % ring it is in register (P + r) % ring.
 // A row is requested when the window drops one, and decoded at its first use.
+// (Inlined by force: with several callers it would become a call, whose
+// registers go through scratch.)
 template <int SPLIT, class S, int BCX, int BCY, int D>
-__device__ __attribute__((always_inline)) inline void planes_walk(const typename S::T* __restrict__ src, typename S::T* __restrict__ dst,
-                                   const KParams& kp, int a, int x0, int ya, int yb,
-                                   const typename S::T* __restrict__ ghost,
-                                   PlanesShared<SPLIT, typename S::C>& sh) {
+__device__ __attribute__((always_inline)) inline void planes_walk(
+    const typename S::T* __restrict__ src, typename S::T* __restrict__ dst, const KParams& kp, int a, int x0, int ya,
+    int yb, PlanesShared<SPLIT, typename S::C, BCY == BC_WALL>& sh) {
   using R = typename S::C;
   using T = typename S::T;
   constexpr int N1 = Set<SPLIT>::N1;
-  constexpr int Q = Set<SPLIT>::Q;
   constexpr int N = D == 0 ? Set<SPLIT>::NF : Set<SPLIT>::NG;
   constexpr uint32_t SZ = sizeof(T);
   constexpr int RG = PLANES_RING;
@@ -153,56 +232,13 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
 #pragma unroll
   for (int p = 0; p <= N; ++p) hp[p] = uniform(R(wa * hn(p, xa)));
 
-  struct Row { rsrc_t r; uint32_t so, stride; };
-  auto row = [&](int yy) -> Row {
-    if constexpr (BCY == BC_WALL) {
-      if (yy < 0 || yy >= ny) {
-        const int g = yy < 0 ? yy + 2 : (yy - ny < 2 ? yy - ny + 2 : 3);
-        const char* p = reinterpret_cast<const char*>(ghost) + size_t(D * Q) * 4 * plane_bytes;
-        const rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), 0, Q * 4 * plane_bytes, RSRC_WORD3);
-        return Row{r, uint32_t(g) * plane_bytes + pl0 * 4 * plane_bytes, 4 * plane_bytes};
-      }
-      return Row{row_rsrc(src, D, dist_bytes, yy, row_bytes), pl0 * plane_bytes, plane_bytes};
-    } else {
-      return Row{row_rsrc(src, D, dist_bytes, wrap<BCY>(yy, ny), row_bytes), pl0 * plane_bytes, plane_bytes};
-    }
-  };
-  auto load = [&](const Row& r, int b, uint32_t lo) -> R {
-    return Bits<T>::keep(Buf<T>::ld(r.r, r.so + uint32_t(b) * r.stride, lo));
+  // (with walls, rows outside the domain read the edge row and are replaced)
+  auto row = [&](int yy) -> rsrc_t { return row_rsrc(src, D, dist_bytes, wrap<BCY>(yy, ny), row_bytes); };
+  auto load = [&](rsrc_t r, int b, uint32_t lo) -> R {
+    return Bits<T>::keep(Buf<T>::ld(r, (pl0 + uint32_t(b)) * plane_bytes, lo));
   };
   auto face = [&](R u, R c, R n) -> R { return add_quarter(c, lim4_walk(c - u, n - c, beta2)); };
 
-  R win[N1][RG], fbelow[N1];
-  {
-    R extra[N1];
-#pragma unroll
-    for (int dy = -2; dy <= RG - 1; ++dy) {
-      const Row r = row(ya + dy);
-      static_for<N1>([&](auto bc) {
-        constexpr int b = decltype(bc)::value;
-        constexpr double xb = L::xi(b);
-        if (xb > 0.0) {
-          if (dy == -2) extra[b] = load(r, b, vo);
-          else if (dy <= RG - 2) win[b][dy + 1] = load(r, b, vo);
-        } else if (xb < 0.0) {
-          if (dy == -1) extra[b] = load(r, b, vo);
-          else if (dy >= 0) win[b][dy] = load(r, b, vo);
-        } else if (dy >= 0) {
-          win[b][dy] = load(r, b, vo);
-        }
-      });
-    }
-    static_for<N1>([&](auto bc) {
-      constexpr int b = decltype(bc)::value;
-      constexpr double xb = L::xi(b);
-      win[b][0] = Bits<T>::decode(win[b][0]);
-      if (xb != 0.0) {
-        win[b][1] = Bits<T>::decode(win[b][1]);
-        const R e = Bits<T>::decode(extra[b]);
-        fbelow[b] = xb > 0.0 ? face(e, win[b][0], win[b][1]) : face(win[b][1], win[b][0], e);
-      }
-    });
-  }
   auto share = [&](const R* v, int s) {
     double s0, s1, s2, s3;
     if constexpr (S::dev) weighted_pair_sums<N1>(v, s0, s1, s2, s3);
@@ -217,6 +253,107 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
       sh.gsum[s][a][1][col] = s1;
     }
   };
+  R win[N1][RG], fbelow[N1];
+  R above[2][N1];  // with a wall above the range: its ghost rows
+  {
+    R extra[N1];
+#pragma unroll
+    for (int dy = -2; dy <= RG - 1; ++dy) {
+      const rsrc_t r = row(ya + dy);
+      static_for<N1>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        constexpr double xb = L::xi(b);
+        if (xb > 0.0) {
+          if (dy == -2) extra[b] = load(r, b, vo);
+          else if (dy <= RG - 2) win[b][dy + 1] = load(r, b, vo);
+        } else if (xb < 0.0) {
+          if (dy == -1) extra[b] = load(r, b, vo);
+          else if (dy >= 0) win[b][dy] = load(r, b, vo);
+        } else if (dy >= 0) {
+          win[b][dy] = load(r, b, vo);
+        }
+      });
+    }
+    if constexpr (BCY == BC_WALL) {
+      // populations of the wall's ghost row k (as stored): X^eq(G) + (X_B - X^eq(B))
+      auto ghosts = [&](int w, R (&out)[2][N1]) {
+        R vb[2][N1];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const rsrc_t r = row(w == 0 ? k : ny - 1 - k);
+#pragma unroll
+          for (int b = 0; b < N1; ++b) vb[k][b] = load(r, b, vo);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+          for (int b = 0; b < N1; ++b) vb[k][b] = Bits<T>::decode(vb[k][b]);
+          share(vb[k], k);
+        }
+        __syncthreads();
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          double e[N + 1];
+#pragma unroll
+          for (int q = 0; q <= N; ++q) e[q] = 0.0;
+          int j = 0;
+#pragma unroll
+          for (int p = 0; p <= N; ++p)
+#pragma unroll
+            for (int q = 0; p + q <= N; ++q, ++j) {
+              const double h = wa * hn(p, xa);
+              if constexpr (D == 0) e[q] += h * sh.wf[k][j][col];
+              else e[q] += h * sh.wg[k][j][col];
+            }
+#pragma unroll
+          for (int b = 0; b < N1; ++b) {
+            double v = double(vb[k][b]);
+#pragma unroll
+            for (int q = 0; q <= N; ++q) v += (S::dev ? 1.0 : L::w(b)) * hn(q, L::xi(b)) * e[q];
+            out[k][b] = Bits<T>::keep(S::enc64(v, 1.0, 0.0));
+          }
+        }
+      };
+      if (ya < 2) {
+        R g[2][N1];
+        ghosts(0, g);
+#pragma unroll
+        for (int b = 0; b < N1; ++b) {
+          if (L::xi(b) > 0.0) {
+            extra[b] = g[1 - ya][b];
+            if (ya == 0) win[b][0] = g[0][b];
+          } else if (L::xi(b) < 0.0 && ya == 0) {
+            extra[b] = g[0][b];
+          }
+        }
+      }
+      if (yb > ny - 2) {
+        ghosts(1, above);
+#pragma unroll
+        for (int dy = 0; dy <= RG - 1; ++dy) {
+          const int k = ya + dy - ny;
+          if (k < 0) continue;
+#pragma unroll
+          for (int b = 0; b < N1; ++b) {
+            const R v = k == 0 ? above[0][b] : above[1][b];
+            if (L::xi(b) > 0.0 && dy <= RG - 2) win[b][dy + 1] = v;
+            if (L::xi(b) < 0.0) win[b][dy] = v;
+          }
+        }
+      }
+    }
+    static_for<N1>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      constexpr double xb = L::xi(b);
+      win[b][0] = Bits<T>::decode(win[b][0]);
+      if (xb != 0.0) {
+        win[b][1] = Bits<T>::decode(win[b][1]);
+        const R e = Bits<T>::decode(extra[b]);
+        fbelow[b] = xb > 0.0 ? face(e, win[b][0], win[b][1]) : face(win[b][1], win[b][0], e);
+      }
+    });
+  }
   {
     R v[N1];
 #pragma unroll
@@ -253,7 +390,7 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
         for (int q = 0; p + q <= N; ++q, ++k) e[q] += hp[p] * (D == 0 ? sh.cf[par][k][col] : sh.cg[par][k][col]);
     }
     const R om1 = D == 0 ? sh.cf[par][n_coeffs(N)][col] : sh.cg[par][n_coeffs(N)][col];
-    const Row rp = row(y + RG - 1), rn = row(y + RG);
+    const rsrc_t rp = row(y + RG - 1), rn = row(y + RG);
     const uint32_t vo_pos = y + RG - 1 <= yb ? vo : 0x80000000u;
     const uint32_t vo_neg = y + RG <= yb + 1 ? vo : 0x80000000u;
     const uint32_t vo_own = y + RG < yb ? vo : 0x80000000u;
@@ -286,7 +423,11 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
       if constexpr (S::dev) out = S::enc_dev(xnew);
       else out = S::enc(xnew, R(1), R(0));
       Buf<T>::st(rd, (pl0 + b) * plane_bytes, vo_st, out);
-      wn[P] = load(xb > 0.0 ? rp : rn, b, xb > 0.0 ? vo_pos : (xb < 0.0 ? vo_neg : vo_own));
+      const int k = xb > 0.0 ? y + RG - 1 - ny : y + RG - ny;
+      if (BCY == BC_WALL && xb != 0.0 && k >= 0)
+        wn[P] = k == 0 ? above[0][b] : above[1][b];
+      else
+        wn[P] = load(xb > 0.0 ? rp : rn, b, xb > 0.0 ? vo_pos : (xb < 0.0 ? vo_neg : vo_own));
     });
   };
   auto walk = [&](auto mov) {
@@ -306,8 +447,8 @@ __device__ __attribute__((always_inline)) inline void planes_walk(const typename
   else walk(std::false_type());
 }
 
-template <int SPLIT, class S, int PRM, int D>
-__device__ __attribute__((always_inline)) inline void planes_coeffs(const KParams& kp, int n, PlanesShared<SPLIT, typename S::C>& sh) {
+template <int SPLIT, class S, int PRM, int D, class SH>
+__device__ __attribute__((always_inline)) inline void planes_coeffs(const KParams& kp, int n, SH& sh) {
   const int lane = threadIdx.x & 63;
   for (int k = 0; k < n; ++k) {
     __syncthreads();
