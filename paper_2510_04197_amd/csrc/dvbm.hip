@@ -33,10 +33,10 @@ namespace dvbm {
 
 constexpr int RED_BLOCKS = 1024;
 constexpr int RED_THREADS = 256;
-// blocks of the adjoint relaxation kernel and most blocks of a launch of the
-// one-sweep adjoint (their partials fit the RED_BLOCKS slots of the workspace)
-constexpr int ADJ_RELAX_BLOCKS = 1024, ADJ_BLOCKS = 1024;
-static_assert(ADJ_RELAX_BLOCKS <= RED_BLOCKS && ADJ_BLOCKS <= RED_BLOCKS, "adjoint partials exceed the workspace");
+// most blocks of a launch of the adjoint kernels that sum parameter
+// derivatives (4 partial sums each, in the workspace)
+constexpr int ADJ_BLOCKS = 1024;
+static_assert(ADJ_BLOCKS <= RED_BLOCKS, "adjoint partials exceed the workspace");
 // workspace layout (doubles): [0, 4 RED_BLOCKS) block partials, then the
 // final reductions, then (at WS_TICKET) the adjoint's block counter
 constexpr int WS_TICKET = 4 * RED_BLOCKS + 32;
@@ -481,41 +481,51 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce(const double* __restrict
 #endif
 
 // ------------------------------------------------------------ adjoint
-// Adjoint step, relaxation part: one thread per cell (grid-stride).  When
-// dparams != NULL the (d/dtau_ref, d/dPr) block partials go to
-// partials[4 * blockIdx.x], and the last block to finish (counted in
-// *ticket, which it resets) adds their sum, in block order, to dparams.
-template <int SPLIT, class S, int PRM, class LT>
-__global__ __launch_bounds__(RED_THREADS) void k_adjoint_relax(const typename S::T* __restrict__ state,
-                                                               const LT* __restrict__ lam1,
-                                                               double* __restrict__ work, KParams kp,
-                                                               double tau_ref, double* partials,
-                                                               unsigned* ticket, double* dparams) {
-  const int cells = kp.nx * kp.ny;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += gridDim.x * blockDim.x)
-    cell_adjoint_relax<SPLIT, S, PRM, LT>(state, lam1, work, kp, c, tau_ref, acc[0], acc[1]);
+// Adds the two coefficient waves' (k) per-lane sums of (d/dtau_ref, d/dPr) over
+// all workgroups of a launch to dparams (nothing when it is NULL): each wave's
+// sum goes to partials[2 (2 b + k)], and the last wave to finish (counted in
+// *ticket, which it resets) adds them in that order.
+__device__ inline void add_params(double (&acc)[2], int k, double* partials, unsigned* ticket, double* dparams) {
   if (!dparams) return;
-  const int mode[4] = {0, 0, 0, 0};
-  block_reduce4(acc, mode, partials + 4 * blockIdx.x);
-  __shared__ bool last;
-  if (threadIdx.x == 0) {
-    __threadfence();
-    last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+  const int lane = int(threadIdx.x & 63);
+  auto wave_sum = [&](double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+  };
+  const int n = 2 * int(gridDim.x), slot = 2 * int(blockIdx.x) + k;
+  acc[0] = wave_sum(acc[0]);
+  acc[1] = wave_sum(acc[1]);
+  // The sums are stored and read at device scope, so the count needs only
+  // their completion before it; a __threadfence would write every dirty line
+  // of the L2 back first (256^2: 45 us with it, 28 us without).
+  unsigned before = 0;
+  if (lane == 0) {
+    __hip_atomic_store(partials + 2 * slot, acc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(partials + 2 * slot + 1, acc[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __syncthreads();
-  if (!last) return;
-  __threadfence();
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < int(gridDim.x); b += blockDim.x) {
-    v[0] += __hip_atomic_load(partials + 4 * b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v[1] += __hip_atomic_load(partials + 4 * b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(int(before)) != n - 1) return;
+  asm volatile("" ::: "memory");
+  const double d0 = dparams[0], d1 = dparams[1];
+  double v[2] = {0.0, 0.0};
+  for (int b0 = lane; b0 < n; b0 += 64 * 8) {  // eight loads in flight at a time
+    double t[8][2];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      for (int j = 0; j < 2; ++j) {
+        const int b = b0 + 64 * u;
+        t[u][j] = __hip_atomic_load(partials + 2 * (b < n ? b : n - 1) + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      for (int j = 0; j < 2; ++j) v[j] += b0 + 64 * u < n ? t[u][j] : 0.0;
   }
-  double tot[4];
-  block_reduce4(v, mode, tot);
-  if (threadIdx.x == 0) {
-    dparams[0] += tot[0];
-    dparams[1] += tot[1];
+  v[0] = wave_sum(v[0]);
+  v[1] = wave_sum(v[1]);
+  if (lane == 0) {
+    dparams[0] = d0 + v[0];
+    dparams[1] = d1 + v[1];
     *ticket = 0u;
   }
 }
@@ -588,50 +598,60 @@ __global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_wave
     const int k = w - 2 * N1, lane = int(threadIdx.x & 63);
     double acc[2] = {0.0, 0.0};
     __builtin_amdgcn_s_setprio(2);
-    with_pr_mode(prm, [&](auto m) {
-      adjoint_coeffs<SPLIT, decltype(m)::value>(kp, k, x0, ya, yb, tau_ref, sh, acc[0], acc[1]);
-    });
-    if (!dparams) return;
-    auto wave_sum = [&](double v) {
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      return v;
+    const bool mine = lane >= 2 && lane < 62 && x0 - 2 + lane < kp.nx;
+    auto own = [&](int) { return mine; };
+    auto out = [&](int, const double* mbar, double keep) {
+#pragma unroll
+      for (int j = 0; j < N_MOMENTS; ++j) sh.res[k][j][lane] = mbar[j];
+      sh.res[k][N_MOMENTS][lane] = keep;
     };
-    const int n = 2 * int(gridDim.x), slot = 2 * int(blockIdx.x) + k;
-    acc[0] = wave_sum(acc[0]);
-    acc[1] = wave_sum(acc[1]);
-    // The sums are stored and read at device scope, so the count needs only
-    // their completion before it; a __threadfence would write every dirty line
-    // of the L2 back first (256^2: 45 us with it, 28 us without).
-    unsigned before = 0;
-    if (lane == 0) {
-      __hip_atomic_store(partials + 2 * slot, acc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(partials + 2 * slot + 1, acc[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (__builtin_amdgcn_readfirstlane(int(before)) != n - 1) return;
-    asm volatile("" ::: "memory");
-    const double d0 = dparams[0], d1 = dparams[1];
-    double v[2] = {0.0, 0.0};
-    for (int b0 = lane; b0 < n; b0 += 64 * 8) {  // eight loads in flight at a time
-      double t[8][2];
+    with_pr_mode(prm, [&](auto m) {
+      adjoint_coeffs<SPLIT, decltype(m)::value, false>(kp, k, yb - ya, tau_ref, sh, acc[0], acc[1], own, out);
+    });
+    add_params(acc, k, partials, ticket, dparams);
+  }
+}
+
+// Relaxation part of the deviation storage: workgroup b takes the chunks of 64
+// cells [b n / grid, (b + 1) n / grid) of n, with the roles of the one-sweep
+// kernel; the coefficient waves write the work rows.  Bound on small grids by
+// the chain of one cell: one thread per cell ran 1300 to 1500 vector
+// instructions behind 100 loads, with one wave per SIMD.  Adjoint step with
+// float32 lam' so and with the planes' sums split over the waves: 333 x 250
+// 48.2 -> 44.1 us (split I 46.9 -> 38.8), 64^2 25.4 -> 23.5, 1024^2 435 -> 422.
+template <int SPLIT, class S, class LT>
+__global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(3))) void k_adjoint_relax(
+    const typename S::T* __restrict__ state, const LT* __restrict__ lam1, double* __restrict__ work, KParams kp,
+    int prm, double tau_ref, double* partials, unsigned* ticket, double* dparams) {
+  constexpr int N1 = Set<SPLIT>::N1;
+  __shared__ AdjointShares<SPLIT> sh;
+  const int cells = kp.nx * kp.ny, n = (cells - 1) / 64 + 1, w = wave_role<N1>();
+  const int i0 = int(int64_t(blockIdx.x) * n / gridDim.x), i1 = int(int64_t(blockIdx.x + 1) * n / gridDim.x);
+  if (w < N1) {
+    relax_walk<SPLIT, S, 0, LT>(state, lam1, kp, w, i0, i1, sh);
+  } else if (w < 2 * N1) {
+    relax_walk<SPLIT, S, 1, LT>(state, lam1, kp, w - N1, i0, i1, sh);
+  } else {
+    const int k = w - 2 * N1, lane = int(threadIdx.x & 63);
+    double acc[2] = {0.0, 0.0};
+    __builtin_amdgcn_s_setprio(2);
+    auto own = [&](int r) { return (i0 + r) * 64 + lane < cells; };
+    auto out = [&](int r, const double* mbar, double keep) {
+      const int c = (i0 + r) * 64, left = cells - c;
+      double* o = work + c;
+      auto put = [&](int j, double v) {  // lanes past the last cell store nothing
+        Buf<double>::st(
+            __builtin_amdgcn_make_buffer_rsrc(o + int64_t(j) * cells, 0, left < 64 ? left * 8 : 512, RSRC_WORD3), 0,
+            lane * 8, v);
+      };
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        for (int j = 0; j < 2; ++j) {
-          const int b = b0 + 64 * u;
-          t[u][j] = __hip_atomic_load(partials + 2 * (b < n ? b : n - 1) + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        for (int j = 0; j < 2; ++j) v[j] += b0 + 64 * u < n ? t[u][j] : 0.0;
-    }
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    if (lane == 0) {
-      dparams[0] = d0 + v[0];
-      dparams[1] = d1 + v[1];
-      *ticket = 0u;
-    }
+      for (int j = 0; j < N_MOMENTS; ++j) put(j, mbar[j]);
+      put(N_MOMENTS, keep);
+    };
+    with_pr_mode(prm, [&](auto m) {
+      adjoint_coeffs<SPLIT, decltype(m)::value, true>(kp, k, i1 - i0, tau_ref, sh, acc[0], acc[1], own, out);
+    });
+    add_params(acc, k, partials, ticket, dparams);
   }
 }
 
@@ -861,7 +881,7 @@ struct dvbm_handle {
   double dt;
   mutable int sweep_kseg;  // row ranges per strip of the column-sweep kernel (0: not chosen yet)
   mutable int planes_ranges;   // the same of the plane-group kernel
-  mutable int adjoint_ranges;  // and of the adjoint kernel
+  mutable int adjoint_ranges;  // and of the adjoint kernel (deviation storage: workgroups of its relaxation part)
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -1141,25 +1161,17 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   } else {
     using T = typename S::T;
     const T* s = static_cast<const T*>(state);
-    const double tau = h->p.tau_ref;
-    unsigned* ticket = reinterpret_cast<unsigned*>(ws + WS_TICKET);
-    const int64_t cells = int64_t(h->p.nx) * h->p.ny;
-    const int64_t nb = (cells + RED_THREADS - 1) / RED_THREADS;
-    const dim3 grid(unsigned(nb < ADJ_RELAX_BLOCKS ? nb : ADJ_RELAX_BLOCKS)), block(RED_THREADS);
-    switch (pr_mode(h->p.Pr)) {
-      case PR_UNIT:
-        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_UNIT, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                           ws, ticket, dparams);
-        break;
-      case PR_LOW:
-        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_LOW, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                           ws, ticket, dparams);
-        break;
-      default:
-        hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, PR_HIGH, LT>), grid, block, 0, h->stream, s, lam1, work, h->kp, tau,
-                           ws, ticket, dparams);
-        break;
+    const auto relax = k_adjoint_relax<SPLIT, S, LT>;
+    if (h->adjoint_ranges == 0) {
+      int ncu, per_cu;
+      device_slots(reinterpret_cast<const void*>(relax), planes_threads<SPLIT>(), ncu, per_cu);
+      const int64_t slots = int64_t(ncu) * per_cu, chunks = (int64_t(h->p.nx) * h->p.ny + 63) / 64;
+      const int64_t blocks = chunks < slots ? chunks : slots;
+      h->adjoint_ranges = int(blocks < ADJ_BLOCKS ? blocks : ADJ_BLOCKS);
     }
+    hipLaunchKernelGGL(relax, dim3(unsigned(h->adjoint_ranges)), dim3(planes_threads<SPLIT>()), 0, h->stream, s, lam1,
+                       work, h->kp, pr_mode(h->p.Pr), h->p.tau_ref, ws, reinterpret_cast<unsigned*>(ws + WS_TICKET),
+                       dparams);
     const int64_t groups = 2 * Set<SPLIT>::N1, nstrips = (h->p.nx + ADJ_STRIP - 1) / ADJ_STRIP;
     int64_t ch = (int64_t(h->p.ny) * groups * nstrips + DVBM_ADJ_WAVES - 1) / DVBM_ADJ_WAVES;
     ch = ch < DVBM_ADJ_CH_MIN ? DVBM_ADJ_CH_MIN : (ch > h->p.ny ? h->p.ny : ch);

