@@ -844,7 +844,7 @@ std::string check_params(const dvbm_params* p) {
     if (!(p->wall_T[0] > 0) || !(p->wall_T[1] > 0)) return "wall temperatures must be > 0";
     if (!std::isfinite(p->wall_ux[0]) || !std::isfinite(p->wall_ux[1])) return "wall velocities must be finite";
     if (p->kernel == DVBM_KERNEL_SWEEP || p->kernel == DVBM_KERNEL_TILE)
-      return "walls are supported by the per-cell kernel only (kernel AUTO or CELL)";
+      return "walls run on the plane-group and the per-cell kernel only (kernel AUTO or CELL)";
   }
   if (p->visc_mode != DVBM_CONST_MU && p->visc_mode != DVBM_CONST_TAU) return "unknown visc_mode";
   if (p->kernel < DVBM_KERNEL_AUTO || p->kernel > DVBM_KERNEL_TILE) return "unknown kernel";
