@@ -129,6 +129,15 @@ __device__ inline R lim4(R a, R b, R beta2) {
 // not bound by its instructions, ran 5 % slower with it (4096^2 2977 us
 // before, 3122 us: twice the moves to and from accumulation registers).
 __device__ inline float lim4_walk(float a, float b, float beta2) { return lim4(a, b, beta2); }
+// Of 16-bit values: rounding keeps order and beta2 > 0, so the median can be
+// scaled instead of its arguments, to the same bits with an instruction less.
+// us per step before / after: fp16 256^2 9.73 / 9.03, split I 509 x 383
+// 12.4 / 12.1; bf16 800^2 40.5 / 39.5.  32-bit storage, and the column sweep
+// of most storages, schedule worse with it (256^2 float32 deviations
+// 9.02 / 9.09, sweep float32 1024^2 105.6 / 109.2, bf16 4096^2 978 / 980).
+__device__ inline float lim4_walk16(float a, float b, float beta2) {
+  return med3(beta2 * med3(a, b, 0.0f), a + b, 0.0f);
+}
 __device__ inline double lim4_walk(double a, double b, double beta2) {
   const double s = a + b, m = fmin(beta2 * fmin(fabs(a), fabs(b)), fabs(s));
   return (a < 0.0) != (b < 0.0) ? 0.0 : copysign(m, s);

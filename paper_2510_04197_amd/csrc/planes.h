@@ -19,7 +19,7 @@
 //   float64  64^2 6.0 (19.3), 256^2 15.0 (23.9), 512^2 39 (58)
 //   float64, 16 populations, 512 x 4  4.9 (13.6)
 //   float32 deviations  64^2 4.4 (9.3), 256^2 9.0 (11.8), 512^2 21.8 (30.5)
-//   float16 deviations, 16 populations, 509 x 383  12.2 (17.1)
+//   float16 deviations, 16 populations, 509 x 383  12.1 (17.1)
 //   thermal Couette flow between walls, float64, 4 x 128  9.1 (38.6)
 // No-slip walls: a range next to a wall forms the ghost rows it reads itself,
 // by the same exchange (shares of the two mirrored rows, the difference of the
@@ -237,7 +237,10 @@ __device__ __attribute__((always_inline)) inline void planes_walk(
   auto load = [&](rsrc_t r, int b, uint32_t lo) -> R {
     return Bits<T>::keep(Buf<T>::ld(r, (pl0 + uint32_t(b)) * plane_bytes, lo));
   };
-  auto face = [&](R u, R c, R n) -> R { return add_quarter(c, lim4_walk(c - u, n - c, beta2)); };
+  auto face = [&](R u, R c, R n) -> R {
+    if constexpr (sizeof(T) == 2) return add_quarter(c, lim4_walk16(c - u, n - c, beta2));
+    else return add_quarter(c, lim4_walk(c - u, n - c, beta2));
+  };
 
   auto share = [&](const R* v, int s) {
     double s0, s1, s2, s3;
