@@ -151,8 +151,10 @@ size_t dvbm_workspace_bytes(const dvbm_params* p);
  * the device float64 fields rho, ux, uy, T (Sec. III A 3: initial conditions
  * are equilibrium populations).  stream is a hipStream_t (NULL = default).
  * Computes dt from the fields when p->dt <= 0 (device reduction, then host
- * arithmetic).  Synchronises.  Errors: EINVAL (parameters, NULL pointers),
- * ENAN (rho <= 0 or T <= 0 or non-finite input), ESTIFF (dt/tau_1 > 2 at
+ * arithmetic).  The launches of the later steps are laid out here, for the
+ * device that is current: a step or an adjoint step makes no runtime call
+ * besides its launches.  Synchronises.  Errors: EINVAL (parameters, NULL
+ * pointers), ENAN (rho <= 0 or T <= 0 or non-finite input), ESTIFF (dt/tau_1 > 2 at
  * some node), EHIP.  On success *out owns only host memory.
  */
 int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const double* uy,

@@ -144,7 +144,7 @@ __device__ inline int wave_role() {
 // f(integral_constant PRM) for a Prandtl mode known at run time: only the
 // coefficient waves depend on it, so the kernel is not instantiated per mode.
 template <class F>
-__device__ inline void with_pr_mode(int prm, F&& f) {
+__host__ __device__ inline void with_pr_mode(int prm, F&& f) {
   if (prm == PR_UNIT) f(std::integral_constant<int, PR_UNIT>());
   else if (prm == PR_LOW) f(std::integral_constant<int, PR_LOW>());
   else f(std::integral_constant<int, PR_HIGH>());
@@ -879,9 +879,10 @@ struct dvbm_handle {
   double* ws;
   hipStream_t stream;
   double dt;
-  mutable int sweep_kseg;  // row ranges per strip of the column-sweep kernel (0: not chosen yet)
-  mutable int planes_ranges;   // the same of the plane-group kernel
-  mutable int adjoint_ranges;  // and of the adjoint kernel (deviation storage: workgroups of its relaxation part)
+  // chosen by dvbm_init, so that a step is its launches and nothing else
+  int step_ranges;         // row ranges per strip (group) of the plane-group or the column-sweep kernel
+  int adjoint_ranges[2];   // row ranges per strip of the adjoint kernel (deviation storage: workgroups of its
+                           // relaxation part) with float64 and with float32 cotangents
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -1066,14 +1067,9 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
       const auto kern = k_collide_advect_sweep<SPLIT, S, BCX, BCY, PRM>;
       const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
       const int ngroups = (nstrips + SWEEP_K - 1) / SWEEP_K;
-      if (h->sweep_kseg == 0)
-        h->sweep_kseg = sweep_ranges(reinterpret_cast<const void*>(kern), 128 * SWEEP_K, ngroups, h->p.ny,
-                                     sizeof(T) == 8 ? DVBM_SWEEP_ROUNDS64
-                                                    : (sizeof(T) == 4 ? DVBM_SWEEP_ROUNDS32 : DVBM_SWEEP_ROUNDS16),
-                                     sweep_ring<S>());
-      const int total = ngroups * h->sweep_kseg;
+      const int total = ngroups * h->step_ranges;
       const dim3 grid(8 * ((total + 7) / 8));
-      hipLaunchKernelGGL(kern, grid, dim3(128 * SWEEP_K), 0, h->stream, s, d, h->kp, ngroups, h->sweep_kseg);
+      hipLaunchKernelGGL(kern, grid, dim3(128 * SWEEP_K), 0, h->stream, s, d, h->kp, ngroups, h->step_ranges);
       return;
     }
   }
@@ -1090,39 +1086,41 @@ void launch_step_bc(const dvbm_handle* h, const void* src, void* dst) {
   if (step_kernel<SPLIT>(h) == KERNEL_PLANES) {
     const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
-    if (h->planes_ranges == 0)
-      h->planes_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
-    hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->planes_ranges)), dim3(planes_threads<SPLIT>()), 0,
-                       h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp, nstrips, h->planes_ranges, prm);
+    hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->step_ranges)), dim3(planes_threads<SPLIT>()), 0,
+                       h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp, nstrips, h->step_ranges, prm);
     return;
   }
   if constexpr (BCY == BC_WALL)
     hipLaunchKernelGGL((k_wall_ghosts<SPLIT, S>), dim3((4 * h->p.nx + 255) / 256), dim3(256), 0, h->stream,
                        static_cast<const T*>(src), reinterpret_cast<T*>(h->ws + WS_GHOST), h->kp);
-  if (prm == PR_UNIT)
-    launch_step_pr<SPLIT, S, BCX, BCY, PR_UNIT>(h, src, dst);
-  else if (prm == PR_LOW)
-    launch_step_pr<SPLIT, S, BCX, BCY, PR_LOW>(h, src, dst);
-  else
-    launch_step_pr<SPLIT, S, BCX, BCY, PR_HIGH>(h, src, dst);
+  with_pr_mode(prm, [&](auto m) { launch_step_pr<SPLIT, S, BCX, BCY, decltype(m)::value>(h, src, dst); });
+}
+
+// f(integral_constant BCX, integral_constant BCY) for the boundary rules of a
+// handle without walls, and with walls in y too.
+template <class F>
+void with_open_bcs(const dvbm_params& p, F&& f) {
+  using Periodic = std::integral_constant<int, BC_PERIODIC>;
+  using Open = std::integral_constant<int, BC_ZERO_GRADIENT>;
+  if (p.bc_x == DVBM_PERIODIC) {
+    if (p.bc_y == DVBM_PERIODIC) f(Periodic(), Periodic());
+    else f(Periodic(), Open());
+  } else {
+    if (p.bc_y == DVBM_PERIODIC) f(Open(), Periodic());
+    else f(Open(), Open());
+  }
+}
+template <class F>
+void with_bcs(const dvbm_params& p, F&& f) {
+  using Wall = std::integral_constant<int, BC_WALL>;
+  if (p.bc_y != DVBM_WALL) with_open_bcs(p, f);
+  else if (p.bc_x == DVBM_PERIODIC) f(std::integral_constant<int, BC_PERIODIC>(), Wall());
+  else f(std::integral_constant<int, BC_ZERO_GRADIENT>(), Wall());
 }
 
 template <int SPLIT, class S>
 void step(const dvbm_handle* h, const void* src, void* dst) {
-  const int bx = h->p.bc_x, by = h->p.bc_y;
-  if (by == DVBM_WALL) {
-    if (bx == DVBM_PERIODIC)
-      launch_step_bc<SPLIT, S, BC_PERIODIC, BC_WALL>(h, src, dst);
-    else
-      launch_step_bc<SPLIT, S, BC_ZERO_GRADIENT, BC_WALL>(h, src, dst);
-  } else if (bx == DVBM_PERIODIC && by == DVBM_PERIODIC)
-    launch_step_bc<SPLIT, S, BC_PERIODIC, BC_PERIODIC>(h, src, dst);
-  else if (bx == DVBM_ZERO_GRADIENT && by == DVBM_PERIODIC)
-    launch_step_bc<SPLIT, S, BC_ZERO_GRADIENT, BC_PERIODIC>(h, src, dst);
-  else if (bx == DVBM_PERIODIC && by == DVBM_ZERO_GRADIENT)
-    launch_step_bc<SPLIT, S, BC_PERIODIC, BC_ZERO_GRADIENT>(h, src, dst);
-  else
-    launch_step_bc<SPLIT, S, BC_ZERO_GRADIENT, BC_ZERO_GRADIENT>(h, src, dst);
+  with_bcs(h->p, [&](auto bx, auto by) { launch_step_bc<SPLIT, S, decltype(bx)::value, decltype(by)::value>(h, src, dst); });
 }
 
 template <int SPLIT, class S, int BCX, int BCY, class LT>
@@ -1133,15 +1131,9 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
 // d/dtau_ref, d/dPr from offset 0, the block counter at WS_TICKET doubles).
 template <int SPLIT, class S, class LT>
 void adjoint(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam0, double* dparams, double* work, double* ws) {
-  const int bx = h->p.bc_x, by = h->p.bc_y;
-  if (bx == DVBM_PERIODIC && by == DVBM_PERIODIC)
-    adjoint_bc<SPLIT, S, BC_PERIODIC, BC_PERIODIC, LT>(h, state, lam1, lam0, dparams, work, ws);
-  else if (bx == DVBM_ZERO_GRADIENT && by == DVBM_PERIODIC)
-    adjoint_bc<SPLIT, S, BC_ZERO_GRADIENT, BC_PERIODIC, LT>(h, state, lam1, lam0, dparams, work, ws);
-  else if (bx == DVBM_PERIODIC && by == DVBM_ZERO_GRADIENT)
-    adjoint_bc<SPLIT, S, BC_PERIODIC, BC_ZERO_GRADIENT, LT>(h, state, lam1, lam0, dparams, work, ws);
-  else
-    adjoint_bc<SPLIT, S, BC_ZERO_GRADIENT, BC_ZERO_GRADIENT, LT>(h, state, lam1, lam0, dparams, work, ws);
+  with_open_bcs(h->p, [&](auto bx, auto by) {
+    adjoint_bc<SPLIT, S, decltype(bx)::value, decltype(by)::value, LT>(h, state, lam1, lam0, dparams, work, ws);
+  });
 }
 
 template <int SPLIT, class S, int BCX, int BCY, class LT>
@@ -1149,9 +1141,7 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   if constexpr (!S::dev) {
     const auto kern = k_adjoint<SPLIT, S, BCX, BCY, LT>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
-    if (h->adjoint_ranges == 0)
-      h->adjoint_ranges = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
-    const int nr = h->adjoint_ranges, total = nstrips * nr;
+    const int nr = h->adjoint_ranges[sizeof(LT) == 4], total = nstrips * nr;
     // more strips than the workspace has partials for: in turns
     for (int first = 0; first < total; first += ADJ_BLOCKS)
       hipLaunchKernelGGL(kern, dim3(unsigned(total - first < ADJ_BLOCKS ? total - first : ADJ_BLOCKS)),
@@ -1162,16 +1152,9 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
     using T = typename S::T;
     const T* s = static_cast<const T*>(state);
     const auto relax = k_adjoint_relax<SPLIT, S, LT>;
-    if (h->adjoint_ranges == 0) {
-      int ncu, per_cu;
-      device_slots(reinterpret_cast<const void*>(relax), planes_threads<SPLIT>(), ncu, per_cu);
-      const int64_t slots = int64_t(ncu) * per_cu, chunks = (int64_t(h->p.nx) * h->p.ny + 63) / 64;
-      const int64_t blocks = chunks < slots ? chunks : slots;
-      h->adjoint_ranges = int(blocks < ADJ_BLOCKS ? blocks : ADJ_BLOCKS);
-    }
-    hipLaunchKernelGGL(relax, dim3(unsigned(h->adjoint_ranges)), dim3(planes_threads<SPLIT>()), 0, h->stream, s, lam1,
-                       work, h->kp, pr_mode(h->p.Pr), h->p.tau_ref, ws, reinterpret_cast<unsigned*>(ws + WS_TICKET),
-                       dparams);
+    hipLaunchKernelGGL(relax, dim3(unsigned(h->adjoint_ranges[sizeof(LT) == 4])), dim3(planes_threads<SPLIT>()), 0,
+                       h->stream, s, lam1, work, h->kp, pr_mode(h->p.Pr), h->p.tau_ref, ws,
+                       reinterpret_cast<unsigned*>(ws + WS_TICKET), dparams);
     const int64_t groups = 2 * Set<SPLIT>::N1, nstrips = (h->p.nx + ADJ_STRIP - 1) / ADJ_STRIP;
     int64_t ch = (int64_t(h->p.ny) * groups * nstrips + DVBM_ADJ_WAVES - 1) / DVBM_ADJ_WAVES;
     ch = ch < DVBM_ADJ_CH_MIN ? DVBM_ADJ_CH_MIN : (ch > h->p.ny ? h->p.ny : ch);
@@ -1181,12 +1164,61 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   }
 }
 
+// The handle's counts of row ranges, from what the current device holds of each kernel.
+template <int SPLIT, class S, class LT>
+int choose_adjoint_ranges(const dvbm_handle* h) {
+  int n = 0;
+  if constexpr (!S::dev) {
+    with_open_bcs(h->p, [&](auto bx, auto by) {
+      const auto kern = k_adjoint<SPLIT, S, decltype(bx)::value, decltype(by)::value, LT>;
+      n = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(),
+                         (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN, h->p.ny);
+    });
+  } else {
+    const auto relax = k_adjoint_relax<SPLIT, S, LT>;
+    int ncu, per_cu;
+    device_slots(reinterpret_cast<const void*>(relax), planes_threads<SPLIT>(), ncu, per_cu);
+    const int64_t slots = int64_t(ncu) * per_cu, chunks = (int64_t(h->p.nx) * h->p.ny + 63) / 64;
+    const int64_t blocks = chunks < slots ? chunks : slots;
+    n = int(blocks < ADJ_BLOCKS ? blocks : ADJ_BLOCKS);
+  }
+  return n;
+}
+template <int SPLIT, class S>
+void choose_ranges(dvbm_handle* h) {
+  const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN, kern_id = step_kernel<SPLIT>(h);
+  h->step_ranges = h->adjoint_ranges[0] = h->adjoint_ranges[1] = 0;
+  with_bcs(h->p, [&](auto bx, auto by) {
+    constexpr int BCX = decltype(bx)::value, BCY = decltype(by)::value;
+    if (kern_id == KERNEL_PLANES) {
+      const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
+      h->step_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
+    } else if constexpr (BCY != BC_WALL) {
+      if (kern_id == DVBM_KERNEL_SWEEP)
+        with_pr_mode(pr_mode(h->p.Pr), [&](auto prm) {
+          constexpr int SWEEP_K = sweep_k<S>(), BYTES = sizeof(typename S::T);
+          const auto kern = k_collide_advect_sweep<SPLIT, S, BCX, BCY, decltype(prm)::value>;
+          h->step_ranges = sweep_ranges(reinterpret_cast<const void*>(kern), 128 * SWEEP_K, (nstrips + SWEEP_K - 1) / SWEEP_K,
+                                        h->p.ny, BYTES == 8 ? DVBM_SWEEP_ROUNDS64
+                                                            : (BYTES == 4 ? DVBM_SWEEP_ROUNDS32 : DVBM_SWEEP_ROUNDS16),
+                                        sweep_ring<S>());
+        });
+    }
+  });
+  if constexpr (sizeof(typename S::T) != 2)
+    if (h->p.bc_y != DVBM_WALL) {
+      h->adjoint_ranges[0] = choose_adjoint_ranges<SPLIT, S, double>(h);
+      h->adjoint_ranges[1] = choose_adjoint_ranges<SPLIT, S, float>(h);
+    }
+}
+
 }  // namespace dvbm_launch
 
 #if defined(DVBM_PART)
 // kernel unit DVBM_PART = 5 (split - 1) + storage + 1; the adjoint takes the
 // float64, float32 and float32-deviation storages (storage 0, 1, 4)
 template void dvbm_launch::step<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE>(const dvbm_handle*, const void*, void*);
+template void dvbm_launch::choose_ranges<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE>(dvbm_handle*);
 #if (DVBM_PART - 1) % 5 < 2 || (DVBM_PART - 1) % 5 == 4
 template void dvbm_launch::adjoint<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE, double>(
     const dvbm_handle*, const void*, const double*, double*, double*, double*, double*);
@@ -1194,8 +1226,9 @@ template void dvbm_launch::adjoint<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE, flo
     const dvbm_handle*, const void*, const float*, float*, double*, double*, double*);
 #endif
 #else
-#define DVBM_EXTERN_STEP(SPLIT, S) \
-  extern template void dvbm_launch::step<SPLIT, S>(const dvbm_handle*, const void*, void*);
+#define DVBM_EXTERN_STEP(SPLIT, S)                                                           \
+  extern template void dvbm_launch::step<SPLIT, S>(const dvbm_handle*, const void*, void*); \
+  extern template void dvbm_launch::choose_ranges<SPLIT, S>(dvbm_handle*);
 #define DVBM_EXTERN_ADJ(SPLIT, S)                                                                           \
   extern template void dvbm_launch::adjoint<SPLIT, S, double>(const dvbm_handle*, const void*, const double*, \
                                                               double*, double*, double*, double*);          \
@@ -1311,6 +1344,11 @@ struct DecodeOp {
     hipLaunchKernelGGL((k_decode<SPLIT, S>), dim3(RED_BLOCKS * 4), dim3(256), 0, h->stream,
                        static_cast<const Tt*>(src), X, h->kp);
   }
+};
+
+template <int SPLIT, class S>
+struct RangesOp {
+  static void run(dvbm_handle* h) { dvbm_launch::choose_ranges<SPLIT, S>(h); }
 };
 
 template <int SPLIT, class S>
@@ -1473,9 +1511,7 @@ int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const d
   h->cur = 0;
   h->ws = ws;
   h->stream = s;
-  h->sweep_kseg = 0;
-  h->planes_ranges = 0;
-  h->adjoint_ranges = 0;
+  dispatch<RangesOp>(h->p, h);
   // the fixed scratch of dvbm_adjoint_step_noalloc on this device (set-up only:
   // that entry point then makes no runtime call besides its launches)
   h->scratch = nullptr;

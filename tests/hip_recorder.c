@@ -14,7 +14,8 @@ typedef struct { uint32_t x, y, z; } dim3;
 
 static char log_text[1 << 20];
 static size_t log_len;
-static int per_cu = 1;
+static struct { char text[64]; int count; } workgroups[8];  /* per compute unit, by a part of the kernel's name; else 1 */
+static int n_workgroups;
 static dim3 pushed_grid, pushed_block;
 static size_t pushed_shared;
 static void* pushed_stream;
@@ -29,7 +30,17 @@ static void record(const char* fmt, ...) {
 
 const char* recorder_log(void) { return log_text; }
 void recorder_clear(void) { log_text[log_len = 0] = 0; }
-void recorder_set_workgroups_per_cu(int n) { per_cu = n; }
+void recorder_forget_workgroups(void) { n_workgroups = 0; }
+void recorder_set_workgroups(const char* text, int count) {
+  if (n_workgroups == 8) abort();
+  snprintf(workgroups[n_workgroups].text, sizeof(workgroups[0].text), "%s", text);
+  workgroups[n_workgroups++].count = count;
+}
+
+static const char* kernel_name(const void* kernel) {
+  Dl_info info;
+  return dladdr(kernel, &info) && info.dli_sname ? info.dli_sname : "?";
+}
 
 int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, void* stream) {
   pushed_grid = grid;
@@ -46,10 +57,8 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, void** st
   return 0;
 }
 int hipLaunchKernel(const void* kernel, dim3 grid, dim3 block, void** args, size_t shared, void* stream) {
-  Dl_info info;
   (void)args, (void)shared, (void)stream;
-  record("launch %s %u %u\n", dladdr(kernel, &info) && info.dli_sname ? info.dli_sname : "?", grid.x * grid.y * grid.z,
-         block.x * block.y * block.z);
+  record("launch %s %u %u\n", kernel_name(kernel), grid.x * grid.y * grid.z, block.x * block.y * block.z);
   return 0;
 }
 int hipGetLastError(void) { return 0; }
@@ -67,8 +76,10 @@ int hipGetSymbolAddress(void** p, const void* sym) { (void)sym; record("hipGetSy
 int hipGetDevice(int* d) { record("hipGetDevice\n"); *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int attr, int d) { (void)attr, (void)d; record("hipDeviceGetAttribute\n"); *v = 256; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int block, size_t shared) {
-  (void)f, (void)block, (void)shared;
+  (void)block, (void)shared;
   record("hipOccupancyMaxActiveBlocksPerMultiprocessor\n");
-  *n = per_cu;
+  *n = 1;
+  for (int k = 0; k < n_workgroups; ++k)
+    if (strstr(kernel_name(f), workgroups[k].text)) *n = workgroups[k].count;
   return 0;
 }

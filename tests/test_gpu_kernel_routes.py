@@ -111,3 +111,19 @@ def test_plane_groups_16bit_value_by_value(monkeypatch, nx, ny, bc, split, stora
     kw = WALLS if bc == "wall" else dict(bc_x=bc, bc_y=bc)
     s, p = make(nx, ny, split=split, storage=storage, Pr=0.6, **kw)
     check_stored(s, p, storage, monkeypatch)
+
+
+@pytest.mark.parametrize("storage", ("f64", "f32", "f32_dev"))
+def test_first_adjoint_call_of_a_handle_without_a_work_array(storage):
+    # each call on a handle of its own: nothing is left for the first adjoint step to set up
+    out = []
+    for entry in ("adjoint_step_noalloc", "adjoint_step"):
+        s, _ = make(117, 17, split=2, storage=storage, Pr=0.71)
+        lam1 = torch.randn((2, s.Q, 17, 117), dtype=torch.float64, generator=torch.Generator().manual_seed(4)).cuda()
+        lam, d = s.new_cotangent(), torch.zeros(2, dtype=torch.float64, device="cuda")
+        getattr(s, entry)(s.state_buffer, lam1, lam, d)
+        torch.cuda.synchronize()
+        s.close()
+        out.append((lam.cpu(), d.cpu()))
+    assert float(out[0][0].abs().max()) > 0 and float(out[0][1].abs().min()) > 0
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
