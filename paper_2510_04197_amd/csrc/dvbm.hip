@@ -213,10 +213,34 @@ __device__ inline void sweep_range(int ny, int kseg, int j, int u, int& ya, int&
 //   16 populations  float64 1024^2 119 / 122, 2048^2 472 / 498, 4096^2 1757 / 1943 (two workgroups per CU fit);
 //                   32-bit 1500 x 1000 99.6 / 104, 2048 x 1024 137 / 124;
 //                   16-bit 2048 x 1024 87 / 97, 2048^2 181 / 183
+// Grids whose strips fill the sweep's groups of four leave the planes of 32-bit
+// storage earlier, narrow ones (at most 12 strips) most:
+//   25 populations  235 x 3702 104 / 92.3, 715 x 1216 95.7 / 85.7, 2160 x 402 89.9 / 86.0 (1000 x 900, 17 strips, 98.3 / 103);
+//   16 populations  deviations 480 x 2145 74.8 / 67.2, 1440 x 1041 97.6 / 90.6; values 480 x 2145 75.1 / 70.2,
+//                   1440 x 1041 97.1 / 96.0, 2160 x 694 97.6 / 102 (1500 x 1000, 25 strips, 98.7 / 105)
 template <int SPLIT>
-__host__ constexpr int64_t sweep_min_cells(int bytes) {
-  return SPLIT == 2 ? (bytes == 8 ? 15 << 16 : bytes == 4 ? 7 << 17 : 9 << 17)
-                    : (bytes == 8 ? INT64_MAX : bytes == 4 ? 3 << 19 : 1 << 22);
+__host__ constexpr int64_t sweep_min_cells(int storage, int nstrips) {
+  const bool full = nstrips % SWEEP_K == 0, narrow = full && nstrips <= 12;
+  if (storage == DVBM_F64) return SPLIT == 2 ? 15 << 16 : INT64_MAX;
+  if (storage == DVBM_BF16_DEV || storage == DVBM_FP16_DEV) return SPLIT == 2 ? 9 << 17 : 1 << 22;
+  return SPLIT == 2 ? (narrow ? 6 << 17 : full ? 13 << 16 : 7 << 17)
+                    : (narrow ? 31 << 15 : full && storage == DVBM_F32_DEV ? 43 << 15 : 3 << 19);
+}
+// 61 to 64 columns take the plane groups two strips, the second nearly empty;
+// the per-cell kernel runs them one wave a row, its workgroups of four rows two
+// per CU: 2048 rows at a time.  It is the faster one just below that and, with
+// many rows, in 16 bits.  us per step of 64 columns, planes / cells:
+//   25 populations  16 bits 1400 rows 13.4 / 14.9, 2048 16.9 / 14.8, 2200 17.8 / 20.8, 3000 22.1 / 21.6, 4096 28.5 / 26.5,
+//                   11000 71.1 / 64.4; 32 bits 1000 12.1 / 11.1, 1100 12.3 / 14.2, 2048 17.4 / 16.5, 2200 18.9 / 22.3,
+//                   4096 29.6 / 29.4, 8192 53.3 / 55.7, 11000 85.6 / 76.2
+//   16 populations  16 bits 2048 13.2 / 13.2, 2200 14.2 / 17.4, 3000 17.5 / 16.6, 4096 22.3 / 20.2, 11000 52.5 / 48.1;
+//                   32 bits 2000 13.8 / 12.8, 2200 14.2 / 17.2, 4096 21.2 / 22.0, 11000 49.8 / 51.2
+// Float64 favours the planes.
+template <int SPLIT>
+__host__ constexpr bool cells_for_64_columns(int bytes, int ny) {
+  if (bytes == 8) return false;
+  if (bytes == 2) return ny >= 3000 || (SPLIT == 2 && ny > 1800 && ny <= 2048);
+  return (ny > 1800 && ny <= 2048) || (SPLIT == 2 && ((ny > 900 && ny <= 1024) || ny >= 10000));
 }
 #ifndef DVBM_SWEEP_K64
 #define DVBM_SWEEP_K64 2  // strips per workgroup, float64 storage
@@ -953,15 +977,36 @@ void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
 // Ranges that would be longer than 32 rows are cut to 16 or less, in as many
 // full rounds: neighbouring workgroups then stay close in memory (float64
 // 1024^2: 206 us in one round of 68 rows, 192 us in seven of 9; f32 4096^2:
-// 1590 us at 8 to 16 rows, 1790 us at 32).
-int planes_ranges(const void* kern, int block, int nstrips, int ny) {
+// 1590 us at 8 to 16 rows, 1790 us at 32).  That counts for less where the two
+// buffers stay in the 256 MiB last-level cache (about 300 MB still do), and for
+// nothing where each strip is one range; up to 48 rows one full round, which has
+// fewer row steps than three, is then faster (D2Q16 f32 1024^2 48.5 us in one,
+// 54.8 us in three; bf16 64 x 11000 52.5 / 57.8; float64 30000 x 33 110 / 120; but
+// f32 1024^2 between walls, 18 strips and 420 MB, 134 / 120).
+int planes_ranges(const void* kern, int block, int nstrips, int ny, int64_t buffer_bytes) {
   int ncu, per_cu;
   device_slots(kern, block, ncu, per_cu);
-  int n = per_cu >= 2 ? 2 * ncu / nstrips : 0;
+  const bool two = per_cu >= 2;
+  const int at_once = two ? 2 * ncu : ncu;
+  int n = at_once / nstrips;
   if (n < 1 || ny / n < 4) n = ncu / nstrips;
-  if (n < 1 || ny / n > 32) {
+  const bool full = int64_t(nstrips) * n * 10 >= int64_t(at_once) * 9;
+  if (n < 1 || ny / n > (full && (n == 1 || 2 * buffer_bytes <= 300000000) ? 48 : 32)) {
     const int64_t slots = int64_t(ncu) * per_cu, rounds = (int64_t(nstrips) * ny + 16 * slots - 1) / (16 * slots);
     n = int(rounds * slots / nstrips);
+  } else if (n <= 4 && !full) {
+    // few ranges of many strips can leave much of the device idle: then the
+    // number with the least time, in row steps of a full round; a range costs
+    // about 5 steps besides its rows, 3 where two workgroups share a CU, and a
+    // last round of one workgroup per CU runs in 0.6 of the time of two (257
+    // strips of 16 rows, bf16: 20.9 us in one range, 17.9 in two; 134 strips of
+    // 32 rows, float64: 48.2 in one, 44.1 in three; 16 rows: 27.2 / 28.6)
+    const auto time = [&](int m) {
+      const int rounds = nstrips * m / at_once, rest = nstrips * m % at_once;
+      return ((ny + m - 1) / m + (two ? 3 : 5)) * (rounds + (rest == 0 ? 0.0 : two && rest <= ncu ? 0.6 : 1.0));
+    };
+    for (int m = n + 1, most = 4 * n + 1; m <= most && ny / m >= 4; ++m)
+      if (time(m) < 0.97 * time(n)) n = m;
   }
   return n < 1 ? 1 : (n > ny ? ny : n);
 }
@@ -1036,8 +1081,10 @@ constexpr int KERNEL_PLANES = -1;  // the plane-group kernel: chosen by AUTO onl
 template <int SPLIT>
 int step_kernel(const dvbm_handle* h) {
   if (h->p.kernel != DVBM_KERNEL_AUTO) return h->p.kernel;
-  const bool big = int64_t(h->p.nx) * h->p.ny >= sweep_min_cells<SPLIT>(storage_bytes(h->p.storage));
-  if (h->p.bc_y == DVBM_WALL || !big) return KERNEL_PLANES;
+  if (h->p.bc_y == DVBM_WALL) return KERNEL_PLANES;
+  const int bytes = storage_bytes(h->p.storage), nx = h->p.nx, ny = h->p.ny;
+  if (nx > SWEEP_OWN && nx <= 64 && cells_for_64_columns<SPLIT>(bytes, ny)) return DVBM_KERNEL_CELL;
+  if (int64_t(nx) * ny < sweep_min_cells<SPLIT>(h->p.storage, (nx + SWEEP_OWN - 1) / SWEEP_OWN)) return KERNEL_PLANES;
   if (h->p.storage == DVBM_F64) return DVBM_KERNEL_SWEEP;
   const uint64_t dist = uint64_t(h->kp.sdist) * uint64_t(storage_bytes(h->p.storage));
   return dist <= (uint64_t(1) << 31) ? DVBM_KERNEL_SWEEP : DVBM_KERNEL_CELL;
@@ -1192,7 +1239,8 @@ void choose_ranges(dvbm_handle* h) {
     constexpr int BCX = decltype(bx)::value, BCY = decltype(by)::value;
     if (kern_id == KERNEL_PLANES) {
       const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
-      h->step_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny);
+      h->step_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny,
+                                     2 * h->kp.sdist * int64_t(sizeof(typename S::T)));
     } else if constexpr (BCY != BC_WALL) {
       if (kern_id == DVBM_KERNEL_SWEEP)
         with_pr_mode(pr_mode(h->p.Pr), [&](auto prm) {

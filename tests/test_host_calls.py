@@ -45,3 +45,51 @@ def test_adjoint_ranges_belong_to_the_cotangent_type(storage, kern):
     a, b, c, d = (groups(r, logs) for r, logs in zip(runs, record(runs)))
     assert a == b and c == d
     assert c["adjoint"] == a["adjoint"] and c["adjoint_f32"] > a["adjoint_f32"]
+
+
+# workgroups a compute unit holds of the step kernels (256 compute units, as the recorder answers)
+FITS = [["planes", 2], ["planesILi2ENS_8StoreF64E", 1]]
+
+
+KERNELS = (  # the kernel AUTO launches
+    # about the column sweep's lines, and the largest distributions
+    (2, "f64", 900, 1000, "planes"), (2, "f64", 1024, 1024, "sweep"), (1, "f64", 4096, 4096, "planes"),
+    (2, "f32", 900, 900, "planes"), (2, "f32_dev", 1000, 900, "planes"), (2, "f32", 2160, 402, "sweep"),
+    (2, "f32", 1000, 920, "sweep"), (1, "f32_dev", 1400, 1000, "planes"), (1, "f32_dev", 1440, 1041, "sweep"),
+    (1, "f32", 1440, 1041, "planes"), (1, "f32_dev", 1500, 1000, "planes"), (1, "f32", 1500, 1050, "sweep"), (2, "bf16_dev", 1024, 1024, "planes"), (2, "fp16_dev", 1200, 1000, "sweep"),
+    (1, "bf16_dev", 2048, 2047, "planes"), (1, "fp16_dev", 2048, 2048, "sweep"), (2, "f32", 6528, 6528, ""),
+    # narrow grids of 32-bit storage, with the sweep's groups of four strips full or not
+    (2, "f32", 480, 1666, "sweep"), (2, "f32_dev", 192, 4096, "sweep"), (2, "f32", 72, 11000, "planes"),
+    (1, "f32_dev", 480, 2145, "sweep"), (1, "f32", 192, 4096, "planes"), (1, "f32", 256, 4096, "planes"),
+    # a second strip of at most four columns
+    (2, "bf16_dev", 64, 4096, ""), (1, "fp16_dev", 61, 4096, ""), (2, "f32", 64, 11000, ""),
+    (2, "bf16_dev", 61, 2000, ""), (2, "bf16_dev", 64, 2052, "planes"), (1, "bf16_dev", 64, 2048, "planes"),
+    (2, "f32_dev", 64, 1024, ""), (2, "f32_dev", 64, 1025, "planes"), (1, "f32", 61, 2000, ""), (1, "f32", 64, 1000, "planes"),
+    (2, "bf16_dev", 64, 1400, "planes"), (2, "bf16_dev", 60, 4096, "planes"), (2, "bf16_dev", 65, 4096, "planes"),
+    (2, "f32", 64, 4096, "planes"), (1, "f32", 64, 11000, "planes"), (2, "f64", 64, 11000, "planes"))
+
+GROUPS = (  # workgroups of the plane-group kernel
+    (2, "f64", 64, 64, 2 * 64), (2, "f32", 256, 256, 5 * 51), (2, "f32", 512, 512, 9 * 56),  # one round
+    (1, "bf16_dev", 15400, 16, 257 * 2), (2, "f64", 8000, 32, 134 * 3), (2, "f64", 8000, 16, 134),  # few ranges
+    (1, "f64", 30000, 33, 500), (1, "f32", 1024, 1024, 18 * 28),  # one round of more than 32 rows
+    (1, "f64", 1024, 1024, 18 * 85), (2, "bf16_dev", 25000, 40, 417 * 3), (2, "f64", 61500, 4, 1025),  # several rounds
+)
+
+
+@pytest.fixture(scope="module")
+def first_steps():
+    """The launches of a step, by (split, storage, nx, ny)."""
+    grids = sorted({c[:4] for c in KERNELS + GROUPS})
+    runs = [dict(params=dict(split=c[0], storage=c[1], nx=c[2], ny=c[3], dt=1e-5), calls=["step"], workgroups_per_cu=FITS)
+            for c in grids]
+    return {c: launches(logs[1]) for c, logs in zip(grids, record(runs))}
+
+
+@pytest.mark.parametrize("case", KERNELS, ids=lambda c: "-".join(map(str, c)))
+def test_auto_takes_the_kernel_that_is_faster(first_steps, case):
+    assert [k for k, _ in first_steps[case[:4]]] == ["k_collide_advect" + ("_" + case[4] if case[4] else "")]
+
+
+@pytest.mark.parametrize("case", GROUPS, ids=lambda c: "-".join(map(str, c)))
+def test_row_ranges_of_the_plane_groups(first_steps, case):
+    assert first_steps[case[:4]] == [("k_collide_advect_planes", case[4])]
