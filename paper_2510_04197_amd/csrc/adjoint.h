@@ -343,15 +343,96 @@ __device__ inline void coeffs_vjp(const NodeMoments& m, const KParams& kp, doubl
 //          lam(c) = (1 - om1) lam'(c) + sum_r mbar_r dm_r/dX + flux cotangent.
 constexpr int ADJ_WORK_ROWS = N_MOMENTS + 1;
 
-// Stored value of population (d, i) at (x, y), decoded to float64.
+// Population (d, i) at (x, y), decoded from its stored deviation to float64.
 template <int SPLIT, class S>
 __device__ inline double adj_X(const typename S::T* __restrict__ state, const KParams& kp, int d, int i, int y,
                                int x) {
-  constexpr int Q = Set<SPLIT>::Q;
   const typename S::T v = state[sidx(kp, d, i, y, x)];
-  if (!S::dev) return double(S::raw(v));
   const double r = d == 0 ? 1.0 : g_ref_over_w<SPLIT>(kp, i);
   return weight<SPLIT>(i) * (r + double(S::raw(v)));
+}
+
+// Relaxation part of one cell by one thread.
+template <int SPLIT, class S, int PRM, class LT>
+__device__ inline void cell_adjoint_relax(const typename S::T* __restrict__ state, const LT* __restrict__ lam1,
+                                          double* __restrict__ work, const KParams& kp, int c, double tau_ref,
+                                          double& g_tau, double& g_pr) {
+  constexpr int N1 = Set<SPLIT>::N1;
+  constexpr int Q = Set<SPLIT>::Q;
+  constexpr int NF = Set<SPLIT>::NF;
+  using L = GH<N1>;
+  const int64_t cells = int64_t(kp.nx) * kp.ny;
+  const int y = c / kp.nx, x = c - y * kp.nx;
+
+  // moments of the cell and the lam'-weighted Hermite projections
+  double f[Q], g[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    f[i] = adj_X<SPLIT, S>(state, kp, 0, i, y, x);
+    g[i] = adj_X<SPLIT, S>(state, kp, 1, i, y, x);
+  }
+  const NodeMoments m = node_moments<N1>(f, g);
+  // mu[p][q] = sum_i lam'_i w_i He_p(xi_a)/p! He_q(xi_b)/q!, factorised over the
+  // tensor-product set: t[a][q] = sum_b lam'_(a,b) w_b He_q(xi_b)/q!, then
+  // mu[p][q] = sum_a w_a He_p(xi_a)/p! t[a][q]
+  double mu_f[5][5], mu_g[3][3], s = 0.0;
+  double tf[N1][NF + 1], tg[N1][3];
+#pragma unroll
+  for (int a = 0; a < N1; ++a) {
+#pragma unroll
+    for (int q = 0; q <= NF; ++q) tf[a][q] = 0.0;
+#pragma unroll
+    for (int q = 0; q <= 2; ++q) tg[a][q] = 0.0;
+#pragma unroll
+    for (int b = 0; b < N1; ++b) {
+      const int i = a * N1 + b;
+      const double lf = double(lam1[int64_t(i) * cells + c]), lg = double(lam1[int64_t(Q + i) * cells + c]);
+      const double xb = L::xi(b), wb = L::w(b);
+#pragma unroll
+      for (int q = 0; q <= NF; ++q) {
+        const double h = wb * hn(q, xb);
+        if (h != 0.0) tf[a][q] += lf * h;
+      }
+#pragma unroll
+      for (int q = 0; q <= 2; ++q) {
+        const double h = wb * hn(q, xb);
+        if (h != 0.0) tg[a][q] += lg * h;
+      }
+      s += lf * f[i] + lg * g[i];
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 5; ++p)
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      mu_f[p][q] = 0.0;
+      if (p + q > NF) continue;
+#pragma unroll
+      for (int a = 0; a < N1; ++a) {
+        const double h = L::w(a) * hn(p, L::xi(a));
+        if (h != 0.0) mu_f[p][q] += h * tf[a][q];
+      }
+    }
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      mu_g[p][q] = 0.0;
+      if (p + q > 2) continue;
+#pragma unroll
+      for (int a = 0; a < N1; ++a) {
+        const double h = L::w(a) * hn(p, L::xi(a));
+        if (h != 0.0) mu_g[p][q] += h * tg[a][q];
+      }
+    }
+  double mbar[N_MOMENTS], d_oms, d_pr, om1;
+  coeffs_vjp<SPLIT, PRM>(m, kp, kp.om_scale, kp.Pr, mu_f, mu_g, s, mbar, d_oms, d_pr, om1);
+#pragma unroll
+  for (int r = 0; r < N_MOMENTS; ++r) work[int64_t(r) * cells + c] = mbar[r];
+  work[int64_t(N_MOMENTS) * cells + c] = 1.0 - om1;
+  // om_scale = dt / tau_ref [/ p_ref]:  d om_scale / d tau_ref = -om_scale / tau_ref
+  g_tau += d_oms * (-kp.om_scale / tau_ref);
+  g_pr += d_pr;
 }
 
 // float64 value held by lane l - 1 (l + 1) of the wave; lane 0 (63) reads 0.

@@ -315,10 +315,7 @@ __device__ __attribute__((always_inline)) inline void adjoint_walk(const typenam
 // are complete at the barrier before its step, its result is there two
 // barriers later.  out(r, mbar, 1 - om1) takes it; where own(r), the cell's
 // shares of d/dtau_ref and d/dPr are added to g_tau, g_pr.
-// PARTED: the reads of the lam' sums wait for the moments.  Beside stores to
-// memory all reads at once spill registers, whose reloads wait behind the
-// stores (adjoint step, 333 x 250 float32 deviations: 46.1 us, parted 43.8).
-template <int SPLIT, int PRM, bool PARTED, class OWN, class OUT>
+template <int SPLIT, int PRM, class OWN, class OUT>
 __device__ __attribute__((always_inline)) inline void adjoint_coeffs(const KParams& kp, int k, int n, double tau_ref,
                                                                      const AdjointShares<SPLIT>& sh, double& g_tau,
                                                                      double& g_pr, OWN&& own, OUT&& out) {
@@ -353,7 +350,6 @@ __device__ __attribute__((always_inline)) inline void adjoint_coeffs(const KPara
         },
         mg);
     const NodeMoments m = as_moments(mf, mg);
-    if constexpr (PARTED) asm volatile("" ::: "memory");
     // mu[p][q] = sum_a w_a He_p(xi_a)/p! (sum_b lam'_(a,b) w_b He_q(xi_b)/q!)
     double mu_f[5][5], mu_g[3][3], s = 0.0;
 #pragma unroll
@@ -400,48 +396,28 @@ __device__ __attribute__((always_inline)) inline void adjoint_coeffs(const KPara
 }
 
 // ------------------------------------------------------------ relaxation part alone
-// The moment cotangents and 1 - om1 of the chunks [i0, i1) of 64 consecutive
-// cells, into the work array (deviation storage): the plane waves' side.  A
-// workgroup takes one range of chunks, with the next chunk's loads in flight.
+// The moment cotangents and 1 - om1 of 64 consecutive cells from cell c0 on,
+// into the work array (deviation storage): the plane waves' side.
 template <int SPLIT, class S, int D, class LT>
 __device__ __attribute__((always_inline)) inline void relax_walk(const typename S::T* __restrict__ state,
                                                                  const LT* __restrict__ lam1, const KParams& kp, int a,
-                                                                 int i0, int i1, AdjointShares<SPLIT>& sh) {
-  using T = typename S::T;
+                                                                 int c0, AdjointShares<SPLIT>& sh) {
+  static_assert(S::dev, "deviation formats");
   constexpr int N1 = Set<SPLIT>::N1;
   constexpr int Q = Set<SPLIT>::Q;
   using L = GH<N1>;
-  const int lane = threadIdx.x & 63;
-  const int cells = kp.nx * kp.ny;
+  const int lane = threadIdx.x & 63, cells = kp.nx * kp.ny;
+  const int c = c0 + lane < cells ? c0 + lane : cells - 1, y = c / kp.nx, x = c - y * kp.nx;
   const double xa = L::xi(a);
-  const LT* lp = lam1 + int64_t(D * Q + a * N1) * cells;
-  T xin[N1];
-  LT lin[N1];
-  auto request = [&](int i) {
-    const int c = i * 64 + lane < cells ? i * 64 + lane : cells - 1;
-    const int y = c / kp.nx, x = c - y * kp.nx;
+  double v[N1], l[N1];
 #pragma unroll
-    for (int b = 0; b < N1; ++b) {
-      xin[b] = state[sidx(kp, D, a * N1 + b, y, x)];
-      lin[b] = lp[int64_t(b) * cells + c];
-    }
-  };
-  request(i0);
-  for (int i = i0; i < i1 + 2; ++i) {
-    if (i < i1) {
-      double v[N1], l[N1];
-#pragma unroll
-      for (int b = 0; b < N1; ++b) {
-        const double xb = L::xi(b), r = D == 0 ? 1.0 : (SPLIT == 2 ? kp.gr0 : kp.gr0 + kp.gr1 * (xa * xa + xb * xb - 2.0));
-        v[b] = S::dev ? L::w(a) * L::w(b) * (r + double(S::raw(xin[b]))) : double(S::raw(xin[b]));
-        l[b] = double(lin[b]);
-      }
-      if (i + 1 < i1) request(i + 1);
-      const int par = (i - i0) & 1;
-      adjoint_share<SPLIT, D>(v, l, D == 0 ? &sh.fsh[par][a][0][lane] : &sh.gsh[par][a][0][lane]);
-    }
-    __syncthreads();
+  for (int b = 0; b < N1; ++b) {
+    const double xb = L::xi(b), r = D == 0 ? 1.0 : (SPLIT == 2 ? kp.gr0 : kp.gr0 + kp.gr1 * (xa * xa + xb * xb - 2.0));
+    v[b] = L::w(a) * L::w(b) * (r + double(S::raw(state[sidx(kp, D, a * N1 + b, y, x)])));
+    l[b] = double(lam1[int64_t(D * Q + a * N1 + b) * cells + c]);
   }
+  adjoint_share<SPLIT, D>(v, l, D == 0 ? &sh.fsh[0][a][0][lane] : &sh.gsh[0][a][0][lane]);
+  for (int k = 0; k < 3; ++k) __syncthreads();  // (as many as the coefficient waves of one row)
 }
 
 }  // namespace dvbm

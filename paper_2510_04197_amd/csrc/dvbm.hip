@@ -505,18 +505,17 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce(const double* __restrict
 #endif
 
 // ------------------------------------------------------------ adjoint
-// Adds the two coefficient waves' (k) per-lane sums of (d/dtau_ref, d/dPr) over
-// all workgroups of a launch to dparams (nothing when it is NULL): each wave's
-// sum goes to partials[2 (2 b + k)], and the last wave to finish (counted in
-// *ticket, which it resets) adds them in that order.
-__device__ inline void add_params(double (&acc)[2], int k, double* partials, unsigned* ticket, double* dparams) {
+// Adds n waves' per-lane sums of (d/dtau_ref, d/dPr) to dparams (nothing when it
+// is NULL): wave `slot` of a launch leaves its sum in partials[2 slot], and the
+// last one to finish (counted in *ticket, which it resets) adds them in that
+// order.
+__device__ inline void add_params(double (&acc)[2], int slot, int n, double* partials, unsigned* ticket, double* dparams) {
   if (!dparams) return;
   const int lane = int(threadIdx.x & 63);
   auto wave_sum = [&](double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
   };
-  const int n = 2 * int(gridDim.x), slot = 2 * int(blockIdx.x) + k;
   acc[0] = wave_sum(acc[0]);
   acc[1] = wave_sum(acc[1]);
   // The sums are stored and read at device scope, so the count needs only
@@ -630,53 +629,71 @@ __global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_wave
       sh.res[k][N_MOMENTS][lane] = keep;
     };
     with_pr_mode(prm, [&](auto m) {
-      adjoint_coeffs<SPLIT, decltype(m)::value, false>(kp, k, yb - ya, tau_ref, sh, acc[0], acc[1], own, out);
+      adjoint_coeffs<SPLIT, decltype(m)::value>(kp, k, yb - ya, tau_ref, sh, acc[0], acc[1], own, out);
     });
-    add_params(acc, k, partials, ticket, dparams);
+    add_params(acc, 2 * int(blockIdx.x) + k, 2 * int(gridDim.x), partials, ticket, dparams);
   }
 }
 
-// Relaxation part of the deviation storage: workgroup b takes the chunks of 64
-// cells [b n / grid, (b + 1) n / grid) of n, with the roles of the one-sweep
-// kernel; the coefficient waves write the work rows.  Bound on small grids by
-// the chain of one cell: one thread per cell ran 1300 to 1500 vector
-// instructions behind 100 loads, with one wave per SIMD.  Adjoint step with
-// float32 lam' so and with the planes' sums split over the waves: 333 x 250
-// 48.2 -> 44.1 us (split I 46.9 -> 38.8), 64^2 25.4 -> 23.5, 1024^2 435 -> 422.
+// Relaxation part of the deviation storage on small grids: workgroup b takes
+// the cells 64 b .. 64 b + 63, with the roles of the one-sweep kernel; the first
+// coefficient wave writes their work rows.  Bound by the chain of one cell, which
+// by one thread runs 1300 to 1500 vector instructions behind 100 loads.
 template <int SPLIT, class S, class LT>
 __global__ __launch_bounds__(planes_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(3))) void k_adjoint_relax(
     const typename S::T* __restrict__ state, const LT* __restrict__ lam1, double* __restrict__ work, KParams kp,
     int prm, double tau_ref, double* partials, unsigned* ticket, double* dparams) {
   constexpr int N1 = Set<SPLIT>::N1;
   __shared__ AdjointShares<SPLIT> sh;
-  const int cells = kp.nx * kp.ny, n = (cells - 1) / 64 + 1, w = wave_role<N1>();
-  const int i0 = int(int64_t(blockIdx.x) * n / gridDim.x), i1 = int(int64_t(blockIdx.x + 1) * n / gridDim.x);
+  const int cells = kp.nx * kp.ny, c0 = 64 * int(blockIdx.x), w = wave_role<N1>();
   if (w < N1) {
-    relax_walk<SPLIT, S, 0, LT>(state, lam1, kp, w, i0, i1, sh);
+    relax_walk<SPLIT, S, 0, LT>(state, lam1, kp, w, c0, sh);
   } else if (w < 2 * N1) {
-    relax_walk<SPLIT, S, 1, LT>(state, lam1, kp, w - N1, i0, i1, sh);
+    relax_walk<SPLIT, S, 1, LT>(state, lam1, kp, w - N1, c0, sh);
   } else {
     const int k = w - 2 * N1, lane = int(threadIdx.x & 63);
     double acc[2] = {0.0, 0.0};
-    __builtin_amdgcn_s_setprio(2);
-    auto own = [&](int r) { return (i0 + r) * 64 + lane < cells; };
-    auto out = [&](int r, const double* mbar, double keep) {
-      const int c = (i0 + r) * 64, left = cells - c;
-      double* o = work + c;
-      auto put = [&](int j, double v) {  // lanes past the last cell store nothing
-        Buf<double>::st(
-            __builtin_amdgcn_make_buffer_rsrc(o + int64_t(j) * cells, 0, left < 64 ? left * 8 : 512, RSRC_WORD3), 0,
-            lane * 8, v);
-      };
+    auto own = [&](int) { return c0 + lane < cells; };
+    auto out = [&](int, const double* mbar, double keep) {
+      if (c0 + lane >= cells) return;
 #pragma unroll
-      for (int j = 0; j < N_MOMENTS; ++j) put(j, mbar[j]);
-      put(N_MOMENTS, keep);
+      for (int j = 0; j < N_MOMENTS; ++j) work[int64_t(j) * cells + c0 + lane] = mbar[j];
+      work[int64_t(N_MOMENTS) * cells + c0 + lane] = keep;
     };
     with_pr_mode(prm, [&](auto m) {
-      adjoint_coeffs<SPLIT, decltype(m)::value, true>(kp, k, i1 - i0, tau_ref, sh, acc[0], acc[1], own, out);
+      adjoint_coeffs<SPLIT, decltype(m)::value>(kp, k, 1, tau_ref, sh, acc[0], acc[1], own, out);
     });
-    add_params(acc, k, partials, ticket, dparams);
+    if (k == 0) add_params(acc, int(blockIdx.x), int(gridDim.x), partials, ticket, dparams);
   }
+}
+
+// The same by one thread per cell (grid-stride), for all other grids: beyond one
+// workgroup of the plane waves per CU it keeps more loads in flight.  Adjoint step
+// of float32 deviations with float32 lam', us per step, plane waves / cells: 64^2
+// 22.2 / 23.8, 100^2 23.7 / 24.1, 128^2 25.0 / 24.5, 150 x 128 27.9 / 24.8, 256^2 43.5 / 34.9
+// (two and more cells to a lane in turn: 333 x 250 42.3 / 38.2, 1024^2 413 / 387, 2048^2
+// 1673 / 1558); without parameter sums 128^2 20.9 / 22.5, 150 x 128 23.7 / 22.9.
+constexpr int ADJ_RELAX_CELLS = 16384;  // most cells of the plane waves' kernel
+template <int SPLIT, class S, int PRM, class LT>
+__global__ __launch_bounds__(RED_THREADS) void k_adjoint_relax_cells(const typename S::T* __restrict__ state,
+                                                                     const LT* __restrict__ lam1,
+                                                                     double* __restrict__ work, KParams kp,
+                                                                     double tau_ref, double* partials,
+                                                                     unsigned* ticket, double* dparams) {
+  const int cells = kp.nx * kp.ny;
+  double acc[2] = {0.0, 0.0};
+  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += gridDim.x * blockDim.x)
+    cell_adjoint_relax<SPLIT, S, PRM, LT>(state, lam1, work, kp, c, tau_ref, acc[0], acc[1]);
+  if (!dparams) return;
+  __shared__ double sums[2][RED_THREADS];
+  const int t = int(threadIdx.x);
+  sums[0][t] = acc[0];
+  sums[1][t] = acc[1];
+  __syncthreads();
+  if (t >= 64) return;
+  for (int j = 0; j < 2; ++j) acc[j] = (sums[j][t] + sums[j][t + 64]) + (sums[j][t + 128] + sums[j][t + 192]);
+  static_assert(RED_THREADS == 256, "four waves");
+  add_params(acc, int(blockIdx.x), int(gridDim.x), partials, ticket, dparams);
 }
 
 template <int SPLIT, class S>
@@ -905,8 +922,7 @@ struct dvbm_handle {
   double dt;
   // chosen by dvbm_init, so that a step is its launches and nothing else
   int step_ranges;         // row ranges per strip (group) of the plane-group or the column-sweep kernel
-  int adjoint_ranges[2];   // row ranges per strip of the adjoint kernel (deviation storage: workgroups of its
-                           // relaxation part) with float64 and with float32 cotangents
+  int adjoint_ranges[2];   // row ranges per strip of the one-sweep adjoint with float64 and with float32 cotangents
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -1198,10 +1214,19 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   } else {
     using T = typename S::T;
     const T* s = static_cast<const T*>(state);
-    const auto relax = k_adjoint_relax<SPLIT, S, LT>;
-    hipLaunchKernelGGL(relax, dim3(unsigned(h->adjoint_ranges[sizeof(LT) == 4])), dim3(planes_threads<SPLIT>()), 0,
-                       h->stream, s, lam1, work, h->kp, pr_mode(h->p.Pr), h->p.tau_ref, ws,
-                       reinterpret_cast<unsigned*>(ws + WS_TICKET), dparams);
+    unsigned* ticket = reinterpret_cast<unsigned*>(ws + WS_TICKET);
+    const int64_t cells = int64_t(h->p.nx) * h->p.ny;
+    if (cells <= ADJ_RELAX_CELLS) {
+      hipLaunchKernelGGL((k_adjoint_relax<SPLIT, S, LT>), dim3(unsigned((cells + 63) / 64)), dim3(planes_threads<SPLIT>()),
+                         0, h->stream, s, lam1, work, h->kp, pr_mode(h->p.Pr), h->p.tau_ref, ws, ticket, dparams);
+    } else {
+      const int64_t nb = (cells + RED_THREADS - 1) / RED_THREADS;
+      with_pr_mode(pr_mode(h->p.Pr), [&](auto m) {
+        hipLaunchKernelGGL((k_adjoint_relax_cells<SPLIT, S, decltype(m)::value, LT>),
+                           dim3(unsigned(nb < ADJ_BLOCKS ? nb : ADJ_BLOCKS)), dim3(RED_THREADS), 0, h->stream, s, lam1,
+                           work, h->kp, h->p.tau_ref, ws, ticket, dparams);
+      });
+    }
     const int64_t groups = 2 * Set<SPLIT>::N1, nstrips = (h->p.nx + ADJ_STRIP - 1) / ADJ_STRIP;
     int64_t ch = (int64_t(h->p.ny) * groups * nstrips + DVBM_ADJ_WAVES - 1) / DVBM_ADJ_WAVES;
     ch = ch < DVBM_ADJ_CH_MIN ? DVBM_ADJ_CH_MIN : (ch > h->p.ny ? h->p.ny : ch);
@@ -1215,20 +1240,11 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
 template <int SPLIT, class S, class LT>
 int choose_adjoint_ranges(const dvbm_handle* h) {
   int n = 0;
-  if constexpr (!S::dev) {
-    with_open_bcs(h->p, [&](auto bx, auto by) {
-      const auto kern = k_adjoint<SPLIT, S, decltype(bx)::value, decltype(by)::value, LT>;
-      n = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(),
-                         (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN, h->p.ny);
-    });
-  } else {
-    const auto relax = k_adjoint_relax<SPLIT, S, LT>;
-    int ncu, per_cu;
-    device_slots(reinterpret_cast<const void*>(relax), planes_threads<SPLIT>(), ncu, per_cu);
-    const int64_t slots = int64_t(ncu) * per_cu, chunks = (int64_t(h->p.nx) * h->p.ny + 63) / 64;
-    const int64_t blocks = chunks < slots ? chunks : slots;
-    n = int(blocks < ADJ_BLOCKS ? blocks : ADJ_BLOCKS);
-  }
+  with_open_bcs(h->p, [&](auto bx, auto by) {
+    const auto kern = k_adjoint<SPLIT, S, decltype(bx)::value, decltype(by)::value, LT>;
+    n = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN,
+                       h->p.ny);
+  });
   return n;
 }
 template <int SPLIT, class S>
@@ -1253,7 +1269,7 @@ void choose_ranges(dvbm_handle* h) {
         });
     }
   });
-  if constexpr (sizeof(typename S::T) != 2)
+  if constexpr (!S::dev)
     if (h->p.bc_y != DVBM_WALL) {
       h->adjoint_ranges[0] = choose_adjoint_ranges<SPLIT, S, double>(h);
       h->adjoint_ranges[1] = choose_adjoint_ranges<SPLIT, S, float>(h);

@@ -106,9 +106,10 @@ def test_adjoint_of_float32_values_on_every_cell(monkeypatch, split, nx, ny, bc,
 
 
 @pytest.mark.parametrize("split", (1, 2))
-@pytest.mark.parametrize("nx,ny,bc", ((131, 127, PERIODIC), (61, 23, OPEN), (333, 250, ("zero_gradient", "periodic"))))
+@pytest.mark.parametrize("nx,ny,bc", ((131, 127, PERIODIC), (61, 23, OPEN), (333, 250, ("zero_gradient", "periodic")),
+                                      (128, 128, PERIODIC), (113, 145, OPEN)))
 def test_adjoint_of_float32_deviations_away_from_kinks(monkeypatch, split, nx, ny, bc):
-    # 260 and 1301 chunks of 64 cells in the relaxation part: more than one to a workgroup on 256 CUs
+    # the relaxation part by plane waves (up to 16384 cells) and by one thread per cell
     lam0, ref, kinked, got, want = step_adjoint_on_stored(monkeypatch, nx, ny, split, bc, "f32_dev")
     assert float(kinked.float().mean()) < 0.01
     ok = ~kinked

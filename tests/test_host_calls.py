@@ -30,8 +30,8 @@ def test_steps_and_adjoint_steps_only_launch():
             assert lines and all(x.startswith("launch ") for x in lines), (sc["params"], name, lines)
 
 
-@pytest.mark.parametrize("storage,kern", (("f64", "k_adjoint"), ("f32", "k_adjoint"), ("f32_dev", "k_adjoint_relax")))
-def test_adjoint_ranges_belong_to_the_cotangent_type(storage, kern):
+@pytest.mark.parametrize("storage", ("f64", "f32"))
+def test_adjoint_ranges_belong_to_the_cotangent_type(storage, kern="k_adjoint"):
     """Each cotangent type's kernel gets the row ranges of its own occupancy, whichever is called first."""
     params = dict(nx=256, ny=4096, split=2, storage=storage, dt=1e-5)
     two = [[f"{kern}I", 1]]
@@ -93,3 +93,13 @@ def test_auto_takes_the_kernel_that_is_faster(first_steps, case):
 @pytest.mark.parametrize("case", GROUPS, ids=lambda c: "-".join(map(str, c)))
 def test_row_ranges_of_the_plane_groups(first_steps, case):
     assert first_steps[case[:4]] == [("k_collide_advect_planes", case[4])]
+
+
+@pytest.mark.parametrize("call", ("adjoint", "adjoint_f32"))
+def test_relaxation_part_of_the_deviation_adjoint(call):
+    """Plane waves, one workgroup per 64 cells, up to 16384 cells; one thread per cell in at most 1024 blocks beyond."""
+    grids = {(4, 5): ("k_adjoint_relax", 1), (128, 128): ("k_adjoint_relax", 256),
+             (113, 145): ("k_adjoint_relax_cells", 65), (2048, 1024): ("k_adjoint_relax_cells", 1024)}
+    runs = [dict(params=dict(split=2, storage="f32_dev", nx=nx, ny=ny, dt=1e-5), calls=[call]) for nx, ny in grids]
+    for want, logs in zip(grids.values(), record(runs)):
+        assert [launches(logs[1])[0], launches(logs[1])[1][0]] == [want, "k_adjoint_flux"]
