@@ -75,19 +75,35 @@ def traffic_entry(kernel_key: str):
     return ent["fetch_bytes"] * sc["fetch"] + ent["write_bytes"] * sc["write"]
 
 
-def step_kernel_name(storage: str, wl) -> str:
-    """The step kernel of a workload here: what AUTO launches on grids of at least 3 * 2^18 cells (split II);
-    below that the storage's one-thread-per-cell kernel (``kernel="tile"`` or ``"cell"``), where
-    AUTO takes the plane-group kernel instead."""
-    cells = wl.nx * wl.ny
-    if 3 << 18 <= cells < {8: 15 << 16, 4: 7 << 17, 2: 9 << 17}[STORAGE_BYTES[storage]]:
+def launched_step_kernel(storage: str, wl, split: int = 2) -> str:
+    """The step kernel the library's AUTO rule launches on a grid without walls."""
+    strips, size = -(-wl.nx // 60), STORAGE_BYTES[storage]
+    if 60 < wl.nx <= 64 and size < 8:  # two strips, the second nearly empty
+        below = 1800 < wl.ny <= 2048
+        if (wl.ny >= 3000 or (split == 2 and below)) if size == 2 else (
+                below or (split == 2 and (900 < wl.ny <= 1024 or wl.ny >= 10000))):
+            return "k_collide_advect"
+    full = strips % 4 == 0
+    narrow = full and strips <= 12
+    if split == 2:
+        line = {8: 15 << 16, 4: 6 << 17 if narrow else 13 << 16 if full else 7 << 17, 2: 9 << 17}[size]
+    else:
+        wide = 43 << 15 if full and storage == "f32_dev" else 3 << 19
+        line = {8: 1 << 63, 4: 31 << 15 if narrow else wide, 2: 1 << 22}[size]
+    if wl.nx * wl.ny < line:
         return "k_collide_advect_planes"
-    big = wl.nx * wl.ny >= 3 << 18
-    if storage == "f64":
-        return "k_collide_advect_sweep" if big else "k_collide_advect_lds"
+    pitch, Q = (wl.nx + 63) // 64 * 64, 16 if split == 1 else 25
+    return "k_collide_advect_sweep" if size == 8 or pitch * wl.ny * Q * size <= 1 << 31 else "k_collide_advect"
+
+
+def step_kernel_name(storage: str, wl) -> str:
+    """The step kernel of a grid (split II) when the plane groups do not take it: the column sweep from 3 * 2^18 cells
+    on, the storage's one-thread-per-cell kernel below and above 2 GiB per distribution in 32 and 16 bits."""
+    cells = wl.nx * wl.ny
+    if cells < 3 << 18:
+        return "k_collide_advect_lds" if storage == "f64" else "k_collide_advect"
     pitch = (wl.nx + 63) // 64 * 64
-    Q = 25
-    if big and pitch * wl.ny * Q * STORAGE_BYTES[storage] <= 1 << 31:
+    if storage == "f64" or pitch * wl.ny * 25 * STORAGE_BYTES[storage] <= 1 << 31:
         return "k_collide_advect_sweep"
     return "k_collide_advect"
 
@@ -795,7 +811,7 @@ def main():
     traffic = traffic_entry(kernel_key)
     roofline = {"bound": "hbm", "achieved": round(main["GBps"], 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(main["frac"], 4), "traffic": traffic,
-                "bytes_per_update": main["bytes_per_update"], "kernel": step_kernel_name(args.storage, wl),
+                "bytes_per_update": main["bytes_per_update"], "kernel": launched_step_kernel(args.storage, wl, phys["split"]),
                 "copy_kernel_GBps": max(ceiling["copy16"], ceiling["copy16_nt"]), "stream_probe_GBps": ceiling,
                 "frac_of_copy": round(main["GBps"] / max(ceiling["copy16"], ceiling["copy16_nt"]), 4)}
     cpu = None

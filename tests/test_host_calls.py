@@ -1,6 +1,7 @@
 """What the entry points ask of the HIP runtime, recorded on the CPU (see hip_calls.py)."""
 
 import os
+from types import SimpleNamespace
 
 import pytest
 
@@ -88,6 +89,13 @@ def first_steps():
 @pytest.mark.parametrize("case", KERNELS, ids=lambda c: "-".join(map(str, c)))
 def test_auto_takes_the_kernel_that_is_faster(first_steps, case):
     assert [k for k, _ in first_steps[case[:4]]] == ["k_collide_advect" + ("_" + case[4] if case[4] else "")]
+
+
+@pytest.mark.parametrize("case", KERNELS + GROUPS, ids=lambda c: "-".join(map(str, c)))
+def test_bench_names_the_kernel_the_library_launches(first_steps, case):
+    import bench
+    split, storage, nx, ny = case[:4]
+    assert [bench.launched_step_kernel(storage, SimpleNamespace(nx=nx, ny=ny), split)] == [k for k, _ in first_steps[case[:4]]]
 
 
 @pytest.mark.parametrize("case", GROUPS, ids=lambda c: "-".join(map(str, c)))
