@@ -127,3 +127,23 @@ def test_first_adjoint_call_of_a_handle_without_a_work_array(storage):
         out.append((lam.cpu(), d.cpu()))
     assert float(out[0][0].abs().max()) > 0 and float(out[0][1].abs().min()) > 0
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_walls_above_2_GiB_of_a_distribution():
+    """6528 x 6528 between walls in float32 deviations, 3.97 GiB a distribution: the plane groups (AUTO) against the
+    per-cell kernel, every stored deviation.  Both round the same terms (at most about 12 per weight, a few roundings of
+    2^-24 each), in another order."""
+    out = []
+    for kernel in ("auto", "cell"):
+        s, p = make(6528, 6528, split=2, storage="f32_dev", Pr=0.6, kernel=kernel, **WALLS)
+        before = s.state_buffer.view(torch.float32).clone()
+        s.step(1)
+        out.append(s.state_buffer.view(torch.float32).clone())
+        s.close()
+        del s
+    worst = moved = 0.0
+    for a, b, x in zip(*(t.split(1 << 28) for t in (*out, before))):
+        worst = max(worst, float((a - b).abs().max()))
+        moved = max(moved, float((a - x).abs().max()))
+    assert moved > 1e-2 and worst <= 2 * 4e-6
+    torch.cuda.empty_cache()
