@@ -82,11 +82,12 @@ enum dvbm_storage { DVBM_F64 = 0, DVBM_F32 = 1, DVBM_BF16_DEV = 2, DVBM_FP16_DEV
 enum dvbm_bc { DVBM_PERIODIC = 0, DVBM_ZERO_GRADIENT = 1, DVBM_WALL = 2 };
 enum dvbm_visc { DVBM_CONST_MU = 0, DVBM_CONST_TAU = 1 };
 /* Step kernel (all compute the same update; the choice only affects speed):
- * AUTO picks the column sweep on large grids without walls (from about 10^6
- * cells, later with split I, never for split I in DVBM_F64; for 32/16-bit
+ * AUTO picks the column sweep on large grids without walls (from 0.8 to 1.2
+ * 10^6 cells, later with split I, never for split I in DVBM_F64; for 32/16-bit
  * storage only when one distribution fits 2 GiB, else the per-cell kernel), and
  * the plane-group kernel, which has no value of its own here, on smaller grids
- * and with walls.
+ * and with walls; some grids of 61 to 64 columns in 32/16-bit storage take the
+ * per-cell kernel.
  * SWEEP with 32/16-bit storage requires a distribution of at most 2 GiB. */
 enum dvbm_kernel { DVBM_KERNEL_AUTO = 0, DVBM_KERNEL_CELL = 1, DVBM_KERNEL_SWEEP = 2, DVBM_KERNEL_TILE = 3 };
 
@@ -151,11 +152,11 @@ size_t dvbm_workspace_bytes(const dvbm_params* p);
  * the device float64 fields rho, ux, uy, T (Sec. III A 3: initial conditions
  * are equilibrium populations).  stream is a hipStream_t (NULL = default).
  * Computes dt from the fields when p->dt <= 0 (device reduction, then host
- * arithmetic).  The launches of the later steps are laid out here, for the
- * device that is current: a step or an adjoint step makes no runtime call
- * besides its launches.  Synchronises.  Errors: EINVAL (parameters, NULL
- * pointers), ENAN (rho <= 0 or T <= 0 or non-finite input), ESTIFF (dt/tau_1 > 2 at
- * some node), EHIP.  On success *out owns only host memory.
+ * arithmetic).  The launches of adjoint steps are laid out here, for the device
+ * that is current (those of steps at the first step, which asks the runtime for
+ * the occupancy of their kernel).  Synchronises.  Errors: EINVAL (parameters,
+ * NULL pointers), ENAN (rho <= 0 or T <= 0 or non-finite input), ESTIFF
+ * (dt/tau_1 > 2 at some node), EHIP.  On success *out owns only host memory.
  */
 int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const double* uy,
               const double* T, void* buf0, void* buf1, void* workspace, void* stream,
@@ -203,8 +204,10 @@ int dvbm_set_state_index(dvbm_handle* h, int index);
 /*
  * Discrete adjoint (reverse-mode derivative of the update above; it is not
  * part of the paper and follows the discretise-then-differentiate rule: the
- * limiter is differentiated on the branch the forward step takes, and dt is
- * held fixed).  Supported for DVBM_F64, DVBM_F32 and DVBM_F32_DEV storage
+ * limiter is differentiated on the branch the forward step takes, with the
+ * derivative 0 at its kink a b = 0, and dt is held fixed; between F32_DEV
+ * neighbours stored equal the sign of a decoding round-off may pick the branch).
+ * Supported for DVBM_F64, DVBM_F32 and DVBM_F32_DEV storage
  * (EINVAL otherwise); the arithmetic is float64.  Cotangents lam are dense device
  * float64 arrays lam[2][Q][ny][nx] of dvbm_adjoint_bytes() bytes.
  */

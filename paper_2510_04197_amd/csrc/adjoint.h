@@ -12,7 +12,10 @@
 //    linear in X, so lam_j = (1 - om1) lam'_j + sum_r mbar_r dm_r/dX_j.
 //  * Flux part: every face value X_{f-1/2} of the NND reconstruction depends
 //    on three neighbours; the limiter is differentiated on the branch the
-//    forward evaluation selects (at a kink a.b = 0 the derivative is zero).
+//    forward evaluation selects (at a kink a.b = 0 the derivative is zero;
+//    of neighbours stored with equal float32 deviations, which are decoded
+//    one by one, the difference can be the rounding of one of them, whose
+//    sign then picks the branch).
 //    Each cell gathers the contributions of the faces that read it; ghost
 //    cells of the zero-gradient rule pass theirs to the interior cell they copy.
 #pragma once
@@ -334,7 +337,7 @@ __device__ inline void coeffs_vjp(const NodeMoments& m, const KParams& kp, doubl
 // ------------------------------------------------------------ adjoint step in two kernels
 // The relaxation part needs the gradient of the coefficient map at every
 // cell; the flux part needs, for every population plane, the plane's
-// stencil.  They run as two kernels:
+// stencil.  The deviation storage runs them as two kernels:
 //   relax: takes the reverse pass coeffs_vjp of every cell, writes
 //          mbar_r and 1 - om1 into a work array work[r][cell] (r = 0..12
 //          moments, 13: 1 - om1) and adds up d/dtau_ref, d/dPr;

@@ -7,6 +7,8 @@
 //                     (_sweep) on large grids, plane groups (_planes) on
 //                     smaller ones and with walls, one thread per cell with
 //                     the stencils through the caches or, in _lds, LDS tiles.
+//   k_adjoint*        one reverse step: one sweep over plane groups, or for
+//                     deviation storage a relaxation part and a flux sweep.
 //   k_init            equilibrium populations of macroscopic fields (Sec. III A 3).
 //   k_moments         rho, u, T fields and per-block float64 conservation sums.
 //   k_speed           per-block extrema of the initial fields (time step, checks).
@@ -109,9 +111,10 @@ __global__ __launch_bounds__(TILE_TX* TILE_TY) void k_collide_advect_lds(const t
 // Plane-group kernel: workgroup b is logical (strip, row range) L, strips
 // fastest, dealt so that every XCD gets one contiguous range of L (neighbouring
 // ranges read each other's edge rows from the XCD's L2).  Two workgroups fit a
-// CU in 32/16-bit storage: the register cap costs a few spilled registers
-// (f32_dev 256^2: 11.3 us uncapped at 86 registers and one workgroup, 9.6 us
-// capped at 80); float64 needs 153 registers and runs one.
+// CU in 32/16-bit storage with the registers capped at 80, a few of them spilled
+// (f32_dev, uncapped at 88 registers and one workgroup / capped: 256^2 9.46 /
+// 9.43 us, 512^2 24.2 / 23.6, but 800^2 49.1 / 53.3); float64 needs 153 registers and
+// runs one.
 template <class S>
 constexpr int planes_wpe() {
   return sizeof(typename S::T) == 8 ? 3 : 6;
@@ -920,9 +923,9 @@ struct dvbm_handle {
   double* ws;
   hipStream_t stream;
   double dt;
-  // chosen by dvbm_init, so that a step is its launches and nothing else
-  int step_ranges;         // row ranges per strip (group) of the plane-group or the column-sweep kernel
-  int adjoint_ranges[2];   // row ranges per strip of the one-sweep adjoint with float64 and with float32 cotangents
+  mutable int step_ranges;  // row ranges per strip (group) of the plane-group or the column-sweep kernel (0: not
+                            // chosen yet; the first step asks the runtime what the kernel's code leaves room for)
+  int adjoint_ranges;       // and of the one-sweep adjoint, chosen by dvbm_init
   double* scratch;         // device address of the fixed scratch array on the handle's device (NULL: lookup failed)
   std::string scratch_err; // why the lookup failed
 };
@@ -970,16 +973,23 @@ KParams make_kparams(const dvbm_params& p, double dt) {
 #ifndef DVBM_SWEEP_ROUNDS16
 #define DVBM_SWEEP_ROUNDS16 1
 #endif
-// Compute units of the current device and workgroups of `kern` each of them
-// holds at a time (256 and 1 where the runtime does not say).
-void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
-  int dev = 0;
-  ncu = per_cu = 0;
+// Compute units of the current device (256 where the runtime does not say).
+int device_cus() {
+  int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0) != hipSuccess || ncu <= 0 || per_cu <= 0) {
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0) {
     (void)hipGetLastError();
-    ncu = 256;
+    return 256;
+  }
+  return ncu;
+}
+// The same, and the workgroups of `kern` each of them holds at a time (1 where
+// the runtime does not say).
+void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
+  ncu = device_cus();
+  per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0) != hipSuccess || per_cu <= 0) {
+    (void)hipGetLastError();
     per_cu = 1;
   }
 }
@@ -989,7 +999,7 @@ void device_slots(const void* kern, int block, int& ncu, int& per_cu) {
 // costs them again, so all workgroups run at once: one per CU, or two where
 // they fit and leave ranges of at least 4 rows (f32_dev, 256^2: 8.95 us with
 // 255 ranges of 5 rows, 9.55 us with 510 of 2.5; 512^2: 22.8 us with 252,
-// 21.8 us with 504; three per CU, split I: 14.3 us against 12.7 us at 509 x 383).
+// 21.8 us with 504; three per CU, D2Q16 bf16: 13.5 us against 12.3 at 509 x 383).
 // Ranges that would be longer than 32 rows are cut to 16 or less, in as many
 // full rounds: neighbouring workgroups then stay close in memory (float64
 // 1024^2: 206 us in one round of 68 rows, 192 us in seven of 9; f32 4096^2:
@@ -1033,12 +1043,14 @@ int planes_ranges(const void* kern, int block, int nstrips, int ny, int64_t buff
 // divide the device well (float64 1024^2, 18 strips: 284 us in one round of
 // 14 ranges, 325 us in two), several where they don't (4096^2, 69 strips:
 // three ranges fill 207 of 256 CUs, eleven 253 of them three times).
-int adjoint_ranges(const void* kern, int block, int nstrips, int ny) {
-  int ncu, per_cu, best = 1;
-  device_slots(kern, block, ncu, per_cu);
+// A CU holds one workgroup, whose LDS leaves no room for a second.
+static_assert(2 * sizeof(AdjointShared<1>) > 160 * 1024 && 2 * sizeof(AdjointShared<2>) > 160 * 1024, "one workgroup per CU");
+int adjoint_ranges(int nstrips, int ny) {
+  const int ncu = device_cus();
+  int best = 1;
   int64_t least = INT64_MAX;
   for (int rounds = 1; rounds <= 4; ++rounds) {
-    int n = rounds * ncu * per_cu / nstrips;
+    int n = rounds * ncu / nstrips;
     n = n < 1 ? 1 : (n > ny ? ny : n);
     const int64_t rows = int64_t(rounds) * ((ny + n - 1) / n + 5);
     if (rows < least) {
@@ -1102,6 +1114,8 @@ int step_kernel(const dvbm_handle* h) {
   if (nx > SWEEP_OWN && nx <= 64 && cells_for_64_columns<SPLIT>(bytes, ny)) return DVBM_KERNEL_CELL;
   if (int64_t(nx) * ny < sweep_min_cells<SPLIT>(h->p.storage, (nx + SWEEP_OWN - 1) / SWEEP_OWN)) return KERNEL_PLANES;
   if (h->p.storage == DVBM_F64) return DVBM_KERNEL_SWEEP;
+  // above 2 GiB the sweep's 32-bit offsets end (the plane groups' rows have bases
+  // of their own and would reach: 6528^2 f32 4346 us against 5057)
   const uint64_t dist = uint64_t(h->kp.sdist) * uint64_t(storage_bytes(h->p.storage));
   return dist <= (uint64_t(1) << 31) ? DVBM_KERNEL_SWEEP : DVBM_KERNEL_CELL;
 }
@@ -1130,6 +1144,11 @@ void launch_step_pr(const dvbm_handle* h, const void* src, void* dst) {
       const auto kern = k_collide_advect_sweep<SPLIT, S, BCX, BCY, PRM>;
       const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
       const int ngroups = (nstrips + SWEEP_K - 1) / SWEEP_K;
+      if (h->step_ranges == 0)
+        h->step_ranges = sweep_ranges(reinterpret_cast<const void*>(kern), 128 * SWEEP_K, ngroups, h->p.ny,
+                                      sizeof(T) == 8 ? DVBM_SWEEP_ROUNDS64
+                                                     : (sizeof(T) == 4 ? DVBM_SWEEP_ROUNDS32 : DVBM_SWEEP_ROUNDS16),
+                                      sweep_ring<S>());
       const int total = ngroups * h->step_ranges;
       const dim3 grid(8 * ((total + 7) / 8));
       hipLaunchKernelGGL(kern, grid, dim3(128 * SWEEP_K), 0, h->stream, s, d, h->kp, ngroups, h->step_ranges);
@@ -1149,6 +1168,9 @@ void launch_step_bc(const dvbm_handle* h, const void* src, void* dst) {
   if (step_kernel<SPLIT>(h) == KERNEL_PLANES) {
     const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
+    if (h->step_ranges == 0)
+      h->step_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny,
+                                     2 * h->kp.sdist * int64_t(sizeof(T)));
     hipLaunchKernelGGL(kern, dim3(unsigned(nstrips) * unsigned(h->step_ranges)), dim3(planes_threads<SPLIT>()), 0,
                        h->stream, static_cast<const T*>(src), static_cast<T*>(dst), h->kp, nstrips, h->step_ranges, prm);
     return;
@@ -1204,7 +1226,7 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   if constexpr (!S::dev) {
     const auto kern = k_adjoint<SPLIT, S, BCX, BCY, LT>;
     const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN;
-    const int nr = h->adjoint_ranges[sizeof(LT) == 4], total = nstrips * nr;
+    const int nr = h->adjoint_ranges, total = nstrips * nr;
     // more strips than the workspace has partials for: in turns
     for (int first = 0; first < total; first += ADJ_BLOCKS)
       hipLaunchKernelGGL(kern, dim3(unsigned(total - first < ADJ_BLOCKS ? total - first : ADJ_BLOCKS)),
@@ -1236,53 +1258,12 @@ void adjoint_bc(const dvbm_handle* h, const void* state, const LT* lam1, LT* lam
   }
 }
 
-// The handle's counts of row ranges, from what the current device holds of each kernel.
-template <int SPLIT, class S, class LT>
-int choose_adjoint_ranges(const dvbm_handle* h) {
-  int n = 0;
-  with_open_bcs(h->p, [&](auto bx, auto by) {
-    const auto kern = k_adjoint<SPLIT, S, decltype(bx)::value, decltype(by)::value, LT>;
-    n = adjoint_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN,
-                       h->p.ny);
-  });
-  return n;
-}
-template <int SPLIT, class S>
-void choose_ranges(dvbm_handle* h) {
-  const int nstrips = (h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN, kern_id = step_kernel<SPLIT>(h);
-  h->step_ranges = h->adjoint_ranges[0] = h->adjoint_ranges[1] = 0;
-  with_bcs(h->p, [&](auto bx, auto by) {
-    constexpr int BCX = decltype(bx)::value, BCY = decltype(by)::value;
-    if (kern_id == KERNEL_PLANES) {
-      const auto kern = k_collide_advect_planes<SPLIT, S, BCX, BCY>;
-      h->step_ranges = planes_ranges(reinterpret_cast<const void*>(kern), planes_threads<SPLIT>(), nstrips, h->p.ny,
-                                     2 * h->kp.sdist * int64_t(sizeof(typename S::T)));
-    } else if constexpr (BCY != BC_WALL) {
-      if (kern_id == DVBM_KERNEL_SWEEP)
-        with_pr_mode(pr_mode(h->p.Pr), [&](auto prm) {
-          constexpr int SWEEP_K = sweep_k<S>(), BYTES = sizeof(typename S::T);
-          const auto kern = k_collide_advect_sweep<SPLIT, S, BCX, BCY, decltype(prm)::value>;
-          h->step_ranges = sweep_ranges(reinterpret_cast<const void*>(kern), 128 * SWEEP_K, (nstrips + SWEEP_K - 1) / SWEEP_K,
-                                        h->p.ny, BYTES == 8 ? DVBM_SWEEP_ROUNDS64
-                                                            : (BYTES == 4 ? DVBM_SWEEP_ROUNDS32 : DVBM_SWEEP_ROUNDS16),
-                                        sweep_ring<S>());
-        });
-    }
-  });
-  if constexpr (!S::dev)
-    if (h->p.bc_y != DVBM_WALL) {
-      h->adjoint_ranges[0] = choose_adjoint_ranges<SPLIT, S, double>(h);
-      h->adjoint_ranges[1] = choose_adjoint_ranges<SPLIT, S, float>(h);
-    }
-}
-
 }  // namespace dvbm_launch
 
 #if defined(DVBM_PART)
 // kernel unit DVBM_PART = 5 (split - 1) + storage + 1; the adjoint takes the
 // float64, float32 and float32-deviation storages (storage 0, 1, 4)
 template void dvbm_launch::step<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE>(const dvbm_handle*, const void*, void*);
-template void dvbm_launch::choose_ranges<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE>(dvbm_handle*);
 #if (DVBM_PART - 1) % 5 < 2 || (DVBM_PART - 1) % 5 == 4
 template void dvbm_launch::adjoint<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE, double>(
     const dvbm_handle*, const void*, const double*, double*, double*, double*, double*);
@@ -1290,9 +1271,8 @@ template void dvbm_launch::adjoint<(DVBM_PART - 1) / 5 + 1, DVBM_PART_STORE, flo
     const dvbm_handle*, const void*, const float*, float*, double*, double*, double*);
 #endif
 #else
-#define DVBM_EXTERN_STEP(SPLIT, S)                                                           \
-  extern template void dvbm_launch::step<SPLIT, S>(const dvbm_handle*, const void*, void*); \
-  extern template void dvbm_launch::choose_ranges<SPLIT, S>(dvbm_handle*);
+#define DVBM_EXTERN_STEP(SPLIT, S) \
+  extern template void dvbm_launch::step<SPLIT, S>(const dvbm_handle*, const void*, void*);
 #define DVBM_EXTERN_ADJ(SPLIT, S)                                                                           \
   extern template void dvbm_launch::adjoint<SPLIT, S, double>(const dvbm_handle*, const void*, const double*, \
                                                               double*, double*, double*, double*);          \
@@ -1408,11 +1388,6 @@ struct DecodeOp {
     hipLaunchKernelGGL((k_decode<SPLIT, S>), dim3(RED_BLOCKS * 4), dim3(256), 0, h->stream,
                        static_cast<const Tt*>(src), X, h->kp);
   }
-};
-
-template <int SPLIT, class S>
-struct RangesOp {
-  static void run(dvbm_handle* h) { dvbm_launch::choose_ranges<SPLIT, S>(h); }
 };
 
 template <int SPLIT, class S>
@@ -1575,7 +1550,8 @@ int dvbm_init(const dvbm_params* p, const double* rho, const double* ux, const d
   h->cur = 0;
   h->ws = ws;
   h->stream = s;
-  dispatch<RangesOp>(h->p, h);
+  h->step_ranges = 0;
+  h->adjoint_ranges = adjoint_ranges((h->p.nx + SWEEP_OWN - 1) / SWEEP_OWN, h->p.ny);
   // the fixed scratch of dvbm_adjoint_step_noalloc on this device (set-up only:
   // that entry point then makes no runtime call besides its launches)
   h->scratch = nullptr;

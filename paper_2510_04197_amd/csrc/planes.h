@@ -242,6 +242,10 @@ __device__ __attribute__((always_inline)) inline void planes_walk(
     else return add_quarter(c, lim4_walk(c - u, n - c, beta2));
   };
 
+  auto coeff = [&](int par, int k) -> R {
+    if constexpr (D == 0) return sh.cf[par][k][col];
+    else return sh.cg[par][k][col];
+  };
   auto share = [&](const R* v, int s) {
     double s0, s1, s2, s3;
     if constexpr (S::dev) weighted_pair_sums<N1>(v, s0, s1, s2, s3);
@@ -390,9 +394,9 @@ __device__ __attribute__((always_inline)) inline void planes_walk(
 #pragma unroll
       for (int p = 0; p <= N; ++p)
 #pragma unroll
-        for (int q = 0; p + q <= N; ++q, ++k) e[q] += hp[p] * (D == 0 ? sh.cf[par][k][col] : sh.cg[par][k][col]);
+        for (int q = 0; p + q <= N; ++q, ++k) e[q] += hp[p] * coeff(par, k);
     }
-    const R om1 = D == 0 ? sh.cf[par][n_coeffs(N)][col] : sh.cg[par][n_coeffs(N)][col];
+    const R om1 = coeff(par, n_coeffs(N));
     const rsrc_t rp = row(y + RG - 1), rn = row(y + RG);
     const uint32_t vo_pos = y + RG - 1 <= yb ? vo : 0x80000000u;
     const uint32_t vo_neg = y + RG <= yb + 1 ? vo : 0x80000000u;
